@@ -364,6 +364,7 @@ hipError_t stencil(const mm_op* op, const StencilArgs& a, hipStream_t s) {
 struct PassIO {
   bool in_f32 = false, out_f32 = false;
   bool ready = false;   // MM_SLICED mode 1: the grid operand is already split (by the stencil)
+  bool few_plain = false;   // FP64: launches of few folded tiles stay plain (GemmArgs::fold = 3)
 };
 
 // Low-precision modes pass FP32 values between the passes of an action.
@@ -411,15 +412,15 @@ const double* folded(const mm_op* op, int mu, int j) {
 }
 
 // (call with the launch's shape set). The grouped passes of one op (its φ1 quadrature
-// nodes and ERK stage groups) fold when all groups together have at least 512 folded
-// tiles (127^3 ETD2RK: five groups of 127 tiles, 0.383 -> 0.345 ms/step), whatever each
-// group alone has; single launches follow the launcher's per-problem rule. The server's
+// nodes and ERK stage groups) that the register-held kernel does not take fold when all
+// groups together have at least 512 folded tiles, whatever each group alone has; single launches follow the launcher's per-problem rule. The server's
 // grouped launches (group_pass) keep the per-problem rule: theirs must not depend on the
 // group count.
-void set_fold(const mm_op* op, GemmArgs& g, int mu) {
+void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
   g.ldf = (g.fold_blocks > 1 ? g.fold_blocks : 1) * fold_ld(op->n[mu]);
   g.fold = op->ctx ? op->ctx->fold : 1;
-  if (g.fold == 1 && g.groups > 1) g.fold = fold_tiles(g) * g.groups >= 512 ? 2 : 0;
+  if (g.fold == 1 && io.few_plain) g.fold = 3;
+  if (g.fold == 1 && g.groups > 1 && !fold_regs_fits(g)) g.fold = fold_tiles(g) * g.groups >= 512 ? 2 : 0;
 }
 
 // the stacked last-axis factor of an ERK stage in the op's precision
@@ -474,7 +475,7 @@ hipError_t pass_mode1(const mm_op* op, int groups, const void* const* in, const 
   g.out_f32 = io.out_f32;
   g.fac_slice = factor_slice_stride(op, n1, n1);
   g.vready = io.ready;
-  set_fold(op, g, 0);
+  set_fold(op, g, 0, io);
   return gemm(op, g, s);
 }
 
@@ -509,7 +510,7 @@ hipError_t pass_mode2(const mm_op* op, int groups, const int* fidx, const void* 
   g.in_f32 = io.in_f32;
   g.out_f32 = io.out_f32;
   g.fac_slice = factor_slice_stride(op, op->n[1], op->n[1]);
-  set_fold(op, g, 1);
+  set_fold(op, g, 1, io);
   return gemm(op, g, s);
 }
 
@@ -531,7 +532,7 @@ hipError_t pass_last(const mm_op* op, const void* F, const int* Fexp, int kmul, 
     g.A[0] = F;
     g.Ff[0] = Ffold;
     g.fold_blocks = kmul;
-    set_fold(op, g, last_axis(op));
+    set_fold(op, g, last_axis(op), io);
     g.fexp[0] = Fexp;
     g.slices = op->slices;
     g.Cadd[0] = nullptr;
@@ -580,7 +581,7 @@ hipError_t pass_last(const mm_op* op, const void* F, const int* Fexp, int kmul, 
   g.A[0] = F;
   g.Ff[0] = Ffold;
   g.fold_blocks = kmul;
-  set_fold(op, g, last_axis(op));
+  set_fold(op, g, last_axis(op), io);
   g.fexp[0] = Fexp;
   g.slices = op->slices;
   g.B[0] = in;
@@ -614,12 +615,14 @@ const double* factor(const mm_op* op, int mu, int j) {
 // modes the intermediates t0, t1 hold floats.
 // out = alpha exp(c_j tau A) in + beta add (add optional).
 // li, lt, lo: layouts of in, of the intermediates t0/t1 and of out (default: unpadded).
+// few_plain: products of few folded tiles stay plain (mumode_expv).
 hipError_t exp_action(const mm_op* op, int j, const void* in, bool in_f32, double* out, int nvec, double* t0,
                       double* t1, hipStream_t s, const double* add = nullptr, double alpha = 1.0,
                       double beta = 1.0, Layout li = Layout{0, 0}, Layout lt = Layout{0, 0},
-                      Layout lo = Layout{0, 0}, bool in_digits = false) {
+                      Layout lo = Layout{0, 0}, bool in_digits = false, bool few_plain = false) {
   const bool mixed = lowp(op);
-  PassIO first{in_f32, mixed, in_digits}, mid{mixed, mixed}, last_io{mixed, false};
+  PassIO first{in_f32, mixed, in_digits, few_plain}, mid{mixed, mixed, false, few_plain},
+      last_io{mixed, false, false, few_plain};
   const int fj[1] = {j};
   const void* i1[1] = {in};
   void* o1[1] = {t0};
@@ -638,8 +641,7 @@ hipError_t exp_action(const mm_op* op, int j, const void* in, bool in_f32, doubl
   }
   hipError_t e = pass_mode1(op, 1, i1, fj, o1, (int)(op->dof / op->n[0]) * nvec, first, s, nullptr, li, lt);
   if (e != hipSuccess) return e;
-  PassIO l2{mixed, false};
-  return pass_last(op, Fl, Fe, 1, t0, out, add, alpha, add ? beta : 0.0, nvec, l2, s, lt, lo, folded(op, la, j));
+  return pass_last(op, Fl, Fe, 1, t0, out, add, alpha, add ? beta : 0.0, nvec, last_io, s, lt, lo, folded(op, la, j));
 }
 
 // out = stacked-last-factor contraction over G groups: group g applies modes 1..d-1 with
@@ -1715,7 +1717,10 @@ mm_status mumode_expv(mm_ctx* ctx, const mm_op* op, int j, const double* in, dou
   hipStream_t s = (hipStream_t)stream;
   double* t0 = (op->family == MM_ERK) ? op->buf[1] : op->buf[0];
   double* t1 = (op->family == MM_ERK) ? op->buf[2] : op->buf[1];
-  HIPCHK(ctx, exp_action(op, j, in, false, out, 1, t0, t1, s));
+  // small grids keep the plain products, whose sums are those of mumode_expv_noalloc (it has
+  // no folded factors): the two agree bit for bit on every grid that the latter takes
+  const Layout dense{0, 0};
+  HIPCHK(ctx, exp_action(op, j, in, false, out, 1, t0, t1, s, nullptr, 1.0, 1.0, dense, dense, dense, false, true));
   return MM_OK;
 }
 

@@ -969,14 +969,18 @@ hipError_t launch_fold(GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Folded launches take over from the plain ones from this many 128 x 64 tiles per group:
-// at 127^3 Lawson2b (254 tiles per pass) the folded step runs 109 against 121 us, while a
+// Folded launches beyond the register-held kernel's limits (axes over 256 points, stacked
+// factors) take over from the plain ones from this many 128 x 64 tiles per group: at 127^3
+// Lawson2b (254 tiles per pass) the tiled folded step runs 109 against 121 us, while a
 // single 127^3 vector (127 tiles) runs faster on the plain kernel's 64-tiles, which spread
-// it over more compute units.
+// it over more compute units. The register-held kernel is the faster one from 17 points on,
+// however few the fibers: its workgroups need no 128 of them (batches of eight 63^3
+// Lawson2b: products 17 us each against 21-49 plain, 31^3: 4.4-4.7 against 4.7-5.4).
 constexpr int64_t kFoldMinTiles = 192;
 
 // Whether g runs folded: FP64, every group with a folded factor, a square factor, and
-// (fold = 1) at least kFoldMinTiles tiles per group.
+// (fold = 1) within the register-held kernel's limits or (fold = 1 or 3) at least
+// kFoldMinTiles tiles per group.
 // The count excludes the group count, so that a problem's products take the same form
 // alone and in a grouped launch with other problems (folded and plain products round
 // differently).
@@ -991,13 +995,13 @@ bool use_fold(const GemmArgs& g, int prec) {
   if (g.K % G != 0 || (g.b_trans ? g.M : g.N) != g.K / G || (G > 1 && !g.b_trans)) return false;
   for (int i = 0; i < g.groups; ++i)
     if (!g.Ff[i]) return false;
-  return g.fold == 2 || fold_tiles(g) >= kFoldMinTiles;
+  return g.fold == 2 || (g.fold == 1 && fold_regs_fits(g)) || fold_tiles(g) >= kFoldMinTiles;
 }
 
 hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.inner <= 0 || g.groups <= 0 || g.groups > kMaxGroups)
     return hipErrorInvalidValue;
-  if (g.fold < 0 || g.fold > 2) return hipErrorInvalidValue;
+  if (g.fold < 0 || g.fold > 3) return hipErrorInvalidValue;
   if (g.tile != 0 && g.tile != 32 && g.tile != 64 && g.tile != 128) return hipErrorInvalidValue;
   if (prec == MM_SLICED && (g.in_f32 || g.out_f32)) return hipErrorInvalidValue;
   // in-batch offsets are 32-bit
@@ -1018,6 +1022,7 @@ hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s) {
   if (use_fold(g, prec)) {
     const int G = fold_blocks(g), n = g.K / G, f = n - n / 2;
     if (g.ldf < G * fold_ld(n) || g.ldf % 2 != 0 || (int64_t)2 * f * g.ldf >= lim) return hipErrorInvalidValue;
+    if (fold_regs_fits(g)) return launch_fold_regs(g, s);
     return launch_fold(g, s);
   }
   if (prec != MM_FP64) {

@@ -52,7 +52,8 @@ struct GemmArgs {
   int vready;
   // FP64 with a centrosymmetric factor (every group's factor E = J E J): Ff[g] is the
   // folded factor [Es; Ed] of launch_fold_factor (2f rows of f = K - K/2 values, row
-  // stride ldf = fold_ld(K)); fold: 0 plain product, 1 folded from 192 tiles per group, 2 always
+  // stride ldf = fold_ld(K)); fold: 0 plain product, 1 folded where that is the faster form
+  // (use_fold), 2 always, 3 folded from 192 tiles per group (fewer: the plain product's sums)
   const double* Ff[kMaxGroups];
   int ldf;
   int fold;
@@ -178,6 +179,11 @@ hipError_t launch_fold_stacked(double* Ff, const double* E, int n, int G, hipStr
 bool use_fold(const GemmArgs& g, int prec);
 // 128 x 64 folded tiles of one group of g.
 int64_t fold_tiles(const GemmArgs& g);
+// Folded product with the factor held in registers (regfac.hip), and whether g is within
+// its limits: one factor block of 9 to 128 folded positions, for modes 2/3 at least two
+// columns, and operands below 2 GB (32-bit byte offsets).
+bool fold_regs_fits(const GemmArgs& g);
+hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s);
 // Tile size the launcher takes for g in precision prec (g.tile if set, else 64 when
 // 128-tiles would not fill the chip once, and in FP64 32 when 64-tiles would not give
 // every compute unit one).
