@@ -708,6 +708,89 @@ hipError_t eig_scale(const mm_op* op, double* out, const double* a, double ca, i
                           op->n[0], op->n[1], op->d == 3 ? op->n[2] : 1, op->tau, s);
 }
 
+// Whether the ERK actions of op run in the folded sine basis (its products have no plain form:
+// mm_set_fold(ctx, 0) keeps the plain exponentials).
+bool sine_active(const mm_op* op) { return op->sine && (!op->ctx || op->ctx->fold != 0); }
+
+// One folded product of the sine transform (inverse: of its inverse) along axis mu: `groups`
+// inputs and outputs, each of `nvec` stacked vectors (one input on the last axis with add)
+hipError_t sine_pass(const mm_op* op, bool inverse, int mu, int groups, const double* const* in, double* const* out,
+                     int nvec, const double* add, hipStream_t s) {
+  const int n = op->n[mu];
+  const int64_t dof = op->dof;
+  GemmArgs g{};
+  for (int i = 0; i < groups; ++i) {
+    g.Ff[i] = inverse ? op->sine_inv[mu] : op->sine_fwd[mu];
+    g.C[i] = out[i];
+    g.Cadd[i] = add;
+    (mu == 0 ? g.A[i] : g.B[i]) = in[i];
+  }
+  g.groups = groups;
+  g.ldf = fold_ld(n);
+  g.fold = 2;
+  g.alpha = 1.0;
+  g.beta = add ? 1.0 : 0.0;
+  g.K = n;
+  g.b_trans = mu > 0;
+  if (mu == 0) {
+    g.M = (int)(dof / n) * nvec;
+    g.N = n;
+    g.lda = g.ldb = g.ldc = n;
+    g.inner = 1;
+  } else {
+    const bool last = mu == op->d - 1;
+    g.M = n;
+    g.lda = n;
+    g.N = last ? (int)(dof / n) : op->n[0];
+    g.ldb = g.ldc = g.N;
+    g.inner = last ? nvec : nvec * op->n[2];
+    g.sB = g.sC = (int64_t)n * g.N;
+  }
+  return gemm(op, g, s);
+}
+
+// T1 <- transform of `count` grid functions (T1, T2: count stacked vectors each)
+hipError_t sine_forward(const mm_op* op, int count, const double* const* in, double* T1, double* T2, hipStream_t s) {
+  double* a = op->d == 3 ? T1 : T2;
+  double* o[2] = {a, a + op->dof};
+  hipError_t e = sine_pass(op, false, 0, count, in, o, 1, nullptr, s);
+  if (e == hipSuccess && op->d == 3) e = sine_pass(op, false, 1, 1, (const double* const*)&T1, &T2, count, nullptr, s);
+  if (e == hipSuccess) e = sine_pass(op, false, op->d - 1, 1, (const double* const*)&T2, &T1, count, nullptr, s);
+  return e;
+}
+
+// out <- inverse transform of T2 (+ add); T1 and T2 are scratch
+hipError_t sine_inverse(const mm_op* op, double* T1, double* T2, double* out, const double* add, hipStream_t s) {
+  hipError_t e = sine_pass(op, true, 0, 1, (const double* const*)&T2, &T1, 1, nullptr, s);
+  if (e == hipSuccess && op->d == 3) e = sine_pass(op, true, 1, 1, (const double* const*)&T1, &T2, 1, nullptr, s);
+  double* last = op->d == 3 ? T2 : T1;
+  if (e == hipSuccess) e = sine_pass(op, true, op->d - 1, 1, (const double* const*)&last, &out, 1, add, s);
+  return e;
+}
+
+// out = ca f_a(tau L) a + cb f_b(tau L) b on transformed functions; MM_EIG_PHI1 is the op's
+// quadrature where it has one
+hipError_t sine_scale(const mm_op* op, double* out, const double* a, double ca, int fa, const double* b, double cb,
+                      int fb, hipStream_t s) {
+  SineScaleArgs p{};
+  p.out = out;
+  p.a = a;
+  p.b = b;
+  p.ca = ca;
+  p.cb = cb;
+  p.fa = op->q > 0 && fa == MM_EIG_PHI1 ? MM_EIG_QUAD : fa;
+  p.fb = op->q > 0 && fb == MM_EIG_PHI1 ? MM_EIG_QUAD : fb;
+  for (int mu = 0; mu < op->d; ++mu) {
+    p.n[mu] = op->n[mu];
+    p.ev[mu] = op->sine_ev[mu];
+    p.tab[mu] = op->sine_tab[mu];
+  }
+  p.q = op->q;
+  for (int j = 1; j <= op->q; ++j) p.weight[j] = op->weight[j];
+  p.tau = op->tau;
+  return launch_sine_scale(op->d, p, s);
+}
+
 // mesh width of axis mu: n unknowns at i/(n+1) (Dirichlet data at both ends) or at i/n
 // (zero normal derivative at x = 1)
 double mesh_h(const mm_op* op, int mu) {
@@ -1059,7 +1142,14 @@ void mumode_destroy(mm_op* op) {
   dev_free(op, op->f3_stage1_exp);
   dev_free(op, op->f3_stage2_exp);
   dev_free(op, op->f3_phi_exp);
-  for (int mu = 0; mu < 3; ++mu) dev_free(op, op->ev[mu]);
+  for (int mu = 0; mu < 3; ++mu) {
+    dev_free(op, op->ev[mu]);
+    if (!op->sine_owned[mu]) continue;
+    dev_free(op, op->sine_fwd[mu]);
+    dev_free(op, op->sine_inv[mu]);
+    dev_free(op, op->sine_ev[mu]);
+    dev_free(op, op->sine_tab[mu]);
+  }
   for (int mu = 0; mu < 3; ++mu)
     if (op->dmat_owned[mu]) dev_free(op, op->dmat[mu]);
   dev_free(op, op->vel);
@@ -1533,6 +1623,39 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
     }
   }
 
+  // ERK on such axes throughout: the folded sine basis (axes of one length share it: A_mu
+  // depends on n_mu alone)
+  if (family == MM_ERK && prec == MM_FP64 && !periodic) {
+    op->sine = true;
+    for (int mu = 0; mu < op->d; ++mu) op->sine = op->sine && op->bc[mu] == MM_BC_DIRICHLET && op->beta_bar[mu] == 0.0;
+  }
+  if (op->sine) {
+    SineNodes nodes{};
+    nodes.q = op->q;
+    for (int j = 0; j <= op->q; ++j) nodes.theta[j] = j == 0 ? 1.0 : op->theta[j];
+    for (int mu = 0; mu < op->d; ++mu) {
+      int same = -1;
+      for (int nu = 0; nu < mu; ++nu)
+        if (op->n[nu] == op->n[mu]) same = nu;
+      if (same >= 0) {
+        op->sine_fwd[mu] = op->sine_fwd[same];
+        op->sine_inv[mu] = op->sine_inv[same];
+        op->sine_ev[mu] = op->sine_ev[same];
+        op->sine_tab[mu] = op->sine_tab[same];
+        continue;
+      }
+      const int n = op->n[mu], f = n - n / 2;
+      const double h = mesh_h(op, mu);
+      op->sine_owned[mu] = true;
+      if ((rc = dev_alloc(op, &op->sine_fwd[mu], (int64_t)2 * f * fold_ld(n))) != MM_OK) return fail(rc);
+      if ((rc = dev_alloc(op, &op->sine_inv[mu], (int64_t)2 * f * fold_ld(n))) != MM_OK) return fail(rc);
+      if ((rc = dev_alloc(op, &op->sine_ev[mu], n)) != MM_OK) return fail(rc);
+      if ((rc = dev_alloc(op, &op->sine_tab[mu], (int64_t)(op->q + 1) * n)) != MM_OK) return fail(rc);
+      HIPCHK(ctx, launch_sine_setup(op->sine_fwd[mu], op->sine_inv[mu], op->sine_ev[mu], op->sine_tab[mu], n,
+                                    op->lam * op->a_max / (h * h), tau, nodes, st));
+    }
+  }
+
   const int la = last_axis(op);
   const int nl = op->n[la];
   const int64_t dof = op->dof;
@@ -1736,6 +1859,13 @@ mm_status mumode_phi1v(mm_ctx* ctx, const mm_op* op, const double* in, double* o
     return MM_EINVAL;
   }
   hipStream_t s = (hipStream_t)stream;
+  if (sine_active(op)) {
+    double *T1 = op->buf[1], *T2 = op->buf[2];
+    HIPCHK(ctx, sine_forward(op, 1, &in, T1, T2, s));
+    HIPCHK(ctx, sine_scale(op, T2, T1, 1.0, MM_EIG_PHI1, nullptr, 0.0, MM_EIG_ONE, s));
+    HIPCHK(ctx, sine_inverse(op, T1, T2, out, nullptr, s));
+    return MM_OK;
+  }
   if (op->exact) {
     // R transform, scale by phi1(tau Lambda), L transform
     double* S1 = op->buf[1];
@@ -1956,8 +2086,58 @@ mm_status enqueue_erk_exact(mm_ctx* ctx, const mm_op* op, double* u, int nsteps,
   return MM_OK;
 }
 
+// ERK steps in the folded sine basis: every phi or exponential action, exact or by
+// quadrature, is a transform, a diagonal scaling and an inverse transform, so an ETD2RK step is
+// the work of 15 mode products of one vector whatever the node count, against 3 (2q + 1)
+// with one product chain per exponential.
+mm_status enqueue_erk_sine(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
+  const double tau = op->tau;
+  const int64_t dof = op->dof;
+  double *g0 = op->buf[0], *T1 = op->buf[1], *T2 = op->buf[2], *U = op->buf[3], *D = op->buf[4], *F0 = op->buf[5];
+  const int sch = op->scheme;
+  for (int it = 0; it < nsteps; ++it) {
+    if (sch != MM_EE) {
+      StencilArgs a = stencil_args(op, u, false);
+      a.out0 = g0;
+      HIPCHK(ctx, stencil(op, a, s));
+    }
+    if (sch == MM_ETD2RK) {
+      // U = S (e^{tau Lambda} S u + tau phi1(tau Lambda) S g0)
+      const double* in[2] = {u, g0};
+      HIPCHK(ctx, sine_forward(op, 2, in, T1, T2, s));
+      HIPCHK(ctx, sine_scale(op, T2, T1, 1.0, MM_EIG_EXP, T1 + dof, tau, MM_EIG_PHI1, s));
+      HIPCHK(ctx, sine_inverse(op, T1, T2, U, nullptr, s));
+    } else {
+      // U = u + S tau phi1(tau Lambda) S F(u) (exponential Euler: straight into u)
+      StencilArgs f = stencil_args(op, u, true);
+      f.out0 = F0;
+      HIPCHK(ctx, stencil(op, f, s));
+      const double* in[1] = {F0};
+      HIPCHK(ctx, sine_forward(op, 1, in, T1, T2, s));
+      HIPCHK(ctx, sine_scale(op, T2, T1, tau, MM_EIG_PHI1, nullptr, 0.0, MM_EIG_ONE, s));
+      HIPCHK(ctx, sine_inverse(op, T1, T2, sch == MM_EE ? u : U, u, s));
+    }
+    if (sch == MM_EE) continue;
+    // D = g(U) - g0;  u+ = U + S c f(tau Lambda) S D with c f = tau/2 phi1 (ETD2RK, ERK2P1)
+    // or tau phi2 (ERK2P2)
+    StencilArgs b = stencil_args(op, U, false);
+    b.sub = g0;
+    b.out0 = D;
+    HIPCHK(ctx, stencil(op, b, s));
+    const double* in[1] = {D};
+    HIPCHK(ctx, sine_forward(op, 1, in, T1, T2, s));
+    if (sch == MM_ERK2P2)
+      HIPCHK(ctx, sine_scale(op, T2, T1, tau, MM_EIG_PHI2, nullptr, 0.0, MM_EIG_ONE, s));
+    else
+      HIPCHK(ctx, sine_scale(op, T2, T1, 0.5 * tau, MM_EIG_PHI1, nullptr, 0.0, MM_EIG_ONE, s));
+    HIPCHK(ctx, sine_inverse(op, T1, T2, u, U, s));
+  }
+  return MM_OK;
+}
+
 // Enqueue nsteps ERK steps on s (arguments already validated).
 mm_status enqueue_erk(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
+  if (sine_active(op)) return enqueue_erk_sine(ctx, op, u, nsteps, s);
   if (op->exact) return enqueue_erk_exact(ctx, op, u, nsteps, s);
   const double tau = op->tau;
   const int q = op->q;

@@ -258,6 +258,33 @@ enum { MM_EIG_ONE = 0, MM_EIG_EXP = 1, MM_EIG_PHI1 = 2, MM_EIG_PHI2 = 3 };
 hipError_t launch_eig_scale(double* out, const double* a, double ca, int fa, const double* b, double cb, int fb,
                             const double* ev1, const double* ev2, const double* ev3, int n1, int n2, int n3,
                             double tau, hipStream_t s);
+// Functions of tau A in the folded sine basis (sinebasis.hip; every axis zero Dirichlet
+// data, no advection in A). MM_EIG_QUAD: the quadrature sum_j w_j exp(theta_j z).
+constexpr int MM_EIG_QUAD = 4;
+struct SineNodes {
+  int q;                       // quadrature nodes (0: none)
+  double theta[kMaxGroups];    // [0] = 1, [1..q] the nodes
+};
+// fwd, inv: folded factors of the transform and its inverse (2 f fold_ld(n) values each); ev:
+// eigenvalues of A_mu (diff = lam a_max / h^2); tab: exp(theta_j tau ev), j = 0..q, n each
+hipError_t launch_sine_setup(double* fwd, double* inv, double* ev, double* tab, int n, double diff, double tau,
+                             const SineNodes& nodes, hipStream_t s);
+// out = ca f_a(tau L) a + cb f_b(tau L) b on transformed grid functions (b may be null; out
+// may be a or b). q > 0: f is MM_EIG_EXP or MM_EIG_QUAD, from the tables.
+struct SineScaleArgs {
+  double* out;
+  const double* a;
+  const double* b;
+  double ca, cb;
+  int fa, fb;
+  int n[3];
+  const double* ev[3];
+  const double* tab[3];
+  int q;
+  double weight[kMaxGroups];   // [1..q]
+  double tau;
+};
+hipError_t launch_sine_scale(int d, const SineScaleArgs& a, hipStream_t s);
 // The same for periodic axes in the real orthonormal Fourier basis (cos/sin pairs are
 // 2 x 2 blocks): sym_mu holds (alpha(m), omega(m)), the symbol of A_mu at wavenumber
 // m = 0 .. n_mu/2 (sym3 null in 2D).
@@ -363,6 +390,14 @@ struct mm_op {
   std::vector<double*> ffold;
   std::vector<bool> ffold_owned;
   int nfold = 0;
+  // ERK, FP64, zero Dirichlet data and no advection in A on every axis: the folded sine basis
+  // (factors of the transform and its inverse, eigenvalues, exponentials of the nodes)
+  bool sine = false;
+  double* sine_fwd[3] = {nullptr, nullptr, nullptr};
+  double* sine_inv[3] = {nullptr, nullptr, nullptr};
+  double* sine_ev[3] = {nullptr, nullptr, nullptr};
+  double* sine_tab[3] = {nullptr, nullptr, nullptr};
+  bool sine_owned[3] = {false, false, false};
   // folded forms of the stacked last-axis ERK factors (null unless that axis folds)
   double* f3_stage1_fold = nullptr;
   double* f3_stage2_fold = nullptr;
