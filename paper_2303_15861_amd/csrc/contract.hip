@@ -969,8 +969,8 @@ hipError_t launch_fold(GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Folded launches beyond the register-held kernel's limits (axes over 256 points, stacked
-// factors) take over from the plain ones from this many 128 x 64 tiles per group: at 127^3
+// Folded launches beyond the register-held kernel's limits (large grids with an axis over
+// 256 points, stacked factors) take over from the plain ones from this many 128 x 64 tiles per group: at 127^3
 // Lawson2b (254 tiles per pass) the tiled folded step runs 109 against 121 us, while a
 // single 127^3 vector (127 tiles) runs faster on the plain kernel's 64-tiles, which spread
 // it over more compute units. The register-held kernel is the faster one from 17 points on,

@@ -180,8 +180,9 @@ bool use_fold(const GemmArgs& g, int prec);
 // 128 x 64 folded tiles of one group of g.
 int64_t fold_tiles(const GemmArgs& g);
 // Folded product with the factor held in registers (regfac.hip), and whether g is within
-// its limits: one factor block of 9 to 128 folded positions, for modes 2/3 at least two
-// columns, and operands below 2 GB (32-bit byte offsets).
+// its limits: one factor block of 9 to 128 folded positions (to 256 where the tiled kernel
+// does not fill the chip), for modes 2/3 at least two columns, and operands below 2 GB
+// (32-bit byte offsets).
 bool fold_regs_fits(const GemmArgs& g);
 hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s);
 // Tile size the launcher takes for g in precision prec (g.tile if set, else 64 when

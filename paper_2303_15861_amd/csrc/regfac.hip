@@ -82,7 +82,7 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
   // distinct 16-byte slots
   constexpr int PK = 8 * H + 4;
   constexpr int NS = FOLD ? 2 : 1;         // staged values per position (s and d, or x)
-  constexpr int KPM = 8 * ((H + 1) / 2);   // staged k pairs, whole row tiles
+  constexpr int KPM = H <= 16 ? 8 * ((H + 1) / 2) : 128;   // staged k pairs (mode 1: threads per fiber)
   constexpr int KI = NT / (TC / 2);        // modes 2/3: k pairs per pass
   constexpr int FI = NT / KPM;             // mode 1: fibers per pass
   static_assert(BT || (NT % KPM == 0 && TC % FI == 0), "mode 1 staging covers whole fibers");
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
   auto idle = [&](int i) { return BT ? (i + 1) * KI > KP && kpair(i) >= KP : KPM != KP && tk >= KP; };
   // Byte offsets of the thread's first k and of its mirror in a fiber; items differ by
   // uniform amounts, which go into the scalar base of the load. Folded: no k is clamped,
-  // as with n >= 16 and 8 (H - 1) < f the staged positions k < 8H and their mirrors lie
+  // as with n >= 17 and 8 (H - 2) < f the staged positions k < 8H and their mirrors lie
   // inside the fiber. Plain: k is clamped to the fiber.
   const unsigned ks = BT ? 8u * (unsigned)ldx : 8u;
   constexpr int DK = BT ? 2 * KI * (NI - 1) + 1 : 0;   // the last k of a thread - its first
@@ -348,22 +348,29 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
   // it is done, so separate phases for loads and staging leave the matrix unit idle. They
   // are therefore cut into pieces that stand between the products: the next tile's items
   // are loaded at the first steps and staged at the last ones.
-  // Fragment steps e (folded: the s and the d tile of step block h = e/2 in turn; plain:
-  // block h = e) alternate between two register sets: a set is read again right after its
-  // products are issued, two steps ahead, so that the products of the other set cover the
-  // LDS latency (the scheduling barriers keep this order).
-  constexpr int T = NS * H;
+  // Fragment steps e alternate between two register sets: a set is read again right after
+  // its products are issued, two steps ahead, so that the products of the other set cover the
+  // LDS latency (the scheduling barriers keep this order). With one unit per wave a step is
+  // a step block of both tiles, whose products alternate between the two accumulators (a
+  // product that follows on its own accumulator waits for it); with more units a step is
+  // one tile's part of a block.
+  constexpr int NB = NC == 1 ? NS : 1;     // tiles per step
+  constexpr int T = NS * H / NB;
   const bool plain_out = p.alpha == 1.0 && !Cadd;
   int cur = 0;
   auto products = [&](auto with_next) {
     constexpr bool MORE = decltype(with_next)::value;
     const double* gs = &Gs[cur][0][0] + (wc * NC * 16 + lr) * PK + 2 * lg;
-    d2 x[2][NC];
+    d2 x[2][NB][NC];
     Item q[NI];
     auto fetch = [&](int e) {
-      const int h = e / NS, t = e % NS;
+      const int h = e * NB / NS;
 #pragma unroll
-      for (int j = 0; j < NC; ++j) x[e & 1][j] = *reinterpret_cast<const d2*>(gs + t * TC * PK + j * 16 * PK + 8 * h);
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+          x[e & 1][b][j] =
+              *reinterpret_cast<const d2*>(gs + ((e * NB + b) % NS) * TC * PK + j * 16 * PK + 8 * h);
     };
     fetch(0);
     fetch(1);
@@ -374,14 +381,17 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
       for (int j = 0; j < NC; ++j) acc[t][j] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int e = 0; e < T; ++e) {
-      const int h = e / NS, t = e % NS;
+      const int h = e * NB / NS;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
-          const double a = F[t][2 * h + s], b = x[e & 1][j][s];
-          acc[t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(BT ? a : b, BT ? b : a, acc[t][j], 0, 0, 0);
-        }
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int j = 0; j < NC; ++j) {
+            const int t = (e * NB + b) % NS;
+            const double f = F[t][2 * h + s], v = x[e & 1][b][j][s];
+            acc[t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(BT ? f : v, BT ? v : f, acc[t][j], 0, 0, 0);
+          }
       __builtin_amdgcn_sched_barrier(0);
       if (e + 2 < T) fetch(e + 2);
       if (MORE) {
@@ -437,14 +447,17 @@ namespace {
 // Workgroup shapes by row tiles RW: WC column waves of NC units and at least WPE waves per
 // SIMD (the register budget: 512 / WPE). From five row tiles on, one workgroup per compute
 // unit has two or three waves per SIMD (LATE); below, several workgroups share the unit.
+// Beyond eight row tiles a wave's factor rows take 144 to 256 registers: one wave per SIMD,
+// row groups of four row tiles, each of which reads the grid tile (neighbouring workgroups:
+// the second and third time from L2).
 template <int FOLD, int H>
 struct Shape {
   static constexpr int RT = (H + 1) / 2;   // row tiles of a square factor (folded: of f <= 8H)
-  static constexpr int RW = RT >= 8 ? 8 : RT;
-  static constexpr int WC = RW == 1 ? 4 : RW == 2 || RW == 5 || RW == 6 ? 2 : 1;
-  static constexpr int NC = RW == 3 || RW == 4 ? 2 : 1;
-  static constexpr int WPE = RW >= 7 || RW == 4 ? 2 : RW >= 3 ? 3 : 4;
-  static constexpr int LATE = RW >= 5;
+  static constexpr int RW = RT > 8 ? 4 : RT;
+  static constexpr int WC = RT == 1 ? 4 : RT == 2 || RT == 5 || RT == 6 ? 2 : 1;
+  static constexpr int NC = RT == 3 || RT == 4 ? 2 : 1;
+  static constexpr int WPE = RT > 8 ? 1 : RT >= 7 || RT == 4 ? 2 : RT >= 3 ? 3 : 4;
+  static constexpr int LATE = RT >= 5 && RT <= 8;
 };
 
 template <int BT, int FOLD, int H>
@@ -489,15 +502,39 @@ hipError_t launch_fold_bt(GemmArgs& g, hipStream_t s) {
     case 14: return launch_regs_h<BT, 1, 14>(g, s);
     case 15: return launch_regs_h<BT, 1, 15>(g, s);
     case 16: return launch_regs_h<BT, 1, 16>(g, s);
+    case 17:
+    case 18: return launch_regs_h<BT, 1, 18>(g, s);
+    case 19:
+    case 20: return launch_regs_h<BT, 1, 20>(g, s);
+    case 21:
+    case 22: return launch_regs_h<BT, 1, 22>(g, s);
+    case 23:
+    case 24: return launch_regs_h<BT, 1, 24>(g, s);
+    case 25:
+    case 26: return launch_regs_h<BT, 1, 26>(g, s);
+    case 27:
+    case 28: return launch_regs_h<BT, 1, 28>(g, s);
+    case 29:
+    case 30: return launch_regs_h<BT, 1, 30>(g, s);
+    case 31:
+    case 32: return launch_regs_h<BT, 1, 32>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
+// Up to 128 folded positions the register-held kernel is the faster one at every size. Beyond,
+// with one wave per SIMD, it wins where the tiled kernel's 128 x 64 tiles do not fill the
+// chip (512 of them): two 511 x 511 vectors 14.5 us per product against 22-24 (plain
+// 32-tiles), but 383^3 in unpadded rows 430-495 us against 480-505 alone and 5% behind in
+// the ETD2RK step.
+constexpr int64_t kWideMaxTiles = 512;
+
 bool fold_regs_fits(const GemmArgs& g) {
   const int n = g.K;
-  if (g.fold_blocks > 1 || n < 17 || n > 256 || (g.b_trans && g.N < 2)) return false;
+  if (g.fold_blocks > 1 || n < 17 || n > 512 || (g.b_trans && g.N < 2)) return false;
+  if (n > 256 && fold_tiles(g) >= kWideMaxTiles) return false;
   const int64_t lim = (int64_t)1 << 28;   // values
   const int64_t in = g.b_trans ? (g.inner - 1) * g.sB + (int64_t)n * g.ldb : (int64_t)g.M * g.lda;
   const int64_t out = g.b_trans ? (g.inner - 1) * g.sC + (int64_t)n * g.ldc : (int64_t)g.M * g.ldc;

@@ -66,3 +66,24 @@ def test_scaled_and_added_output(mm, n):
         ctx.close()
     # both sum in FP64: a few units of rounding per sum of n terms, over two steps
     assert np.max(np.abs(got[1] - got[0])) <= 1e-12 * np.max(np.abs(got[0]))
+
+
+@pytest.mark.parametrize("n", [(511, 300), (383, 449), (257, 512)])
+def test_wide_factors_in_lawson_steps(mm, n):
+    """axes of 257 to 512 points on grids of few tiles (one wave per SIMD, row groups), in the
+    padded layout of the Lawson steps, against the plain products."""
+    import torch
+    p = synth.smooth_problem(n, 55, tau=1e-4, scheme="l2b", beta=(0.5, 0.5))
+    got = {}
+    for mode in (0, 1):
+        ctx = mm.Context(0)
+        ctx.set_fold(mode)
+        op = mm.setup_problem(ctx, p)
+        u = torch.from_numpy(p.u0).cuda()
+        mm.step(op, u, 2)
+        got[mode] = u.cpu().numpy()
+        op.close()
+        ctx.close()
+    # the last stage adds tau/2 g(U): differences of U grow by 1 + 2 d tau (a_max - a_min)/h^2
+    grow = 1.0 + 4 * 1e-4 * 1.8 * (max(n) + 1) ** 2
+    assert np.max(np.abs(got[1] - got[0])) <= 2 * grow * 1e-13 * np.max(np.abs(got[0]))

@@ -24,7 +24,8 @@ def mm():
 
 
 @pytest.mark.parametrize("q", [0, 1, 6])
-@pytest.mark.parametrize("n", [(1, 1), (2, 3), (40, 33), (1, 2, 3), (16, 17, 2), (35, 21, 18), (9, 300, 32), (257, 3, 20)])
+@pytest.mark.parametrize("n", [(1, 1), (2, 3), (40, 33), (1, 2, 3), (16, 17, 2), (35, 21, 18), (9, 300, 32), (257, 3, 20),
+                               (511, 33), (40, 512), (385, 6, 450)])
 def test_phi1_action(mm, n, q):
     import torch
     p = synth.smooth_problem(n, 61, tau=2e-3, scheme="etd2rk", q=q)
