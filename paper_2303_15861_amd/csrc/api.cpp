@@ -1891,6 +1891,133 @@ mm_status mumode_phi1v(mm_ctx* ctx, const mm_op* op, const double* in, double* o
 
 namespace {
 
+// Lawson steps whose stage vectors and first two products run slab by slab in one kernel
+// (slab.hip): FP64 finite-difference grids with n1, n2 <= 64, in the schemes with independent
+// actions of one stage (or one action: SLE). The slab launch replaces a stencil and two to
+// four products, the product along x3 of both actions is one launch: a step of the
+// stabilised Lawson2 has four launches instead of twelve (60^3, Sec. 5.2: 66 -> 39 us).
+// Lawson-Euler and Lawson2b keep the separate passes, which are no slower for one problem
+// (63^3: 24 against 26 us) and faster in the grouped launches, which have to give the same
+// bits (eight problems: 108 against 89 us per step with the slab kernel, whose workgroups
+// hold a compute unit each).
+bool slab_active(const mm_op* op) {
+  return op->family == MM_LAWSON && op->prec == MM_FP64 && !op->periodic &&
+         (op->scheme == MM_SLE || op->scheme == MM_LAWSON2A || op->scheme == MM_SL2) &&
+         slab_fits(op->d, op->n[0], op->n[1], op->n[2]);
+}
+
+SlabArgs slab_args(const mm_op* op, const double* u, bool full) {
+  const StencilArgs st = stencil_args(op, u, full);
+  SlabArgs a{};
+  a.u = u;
+  a.a = st.a;
+  a.n1 = st.n1;
+  a.n2 = st.n2;
+  a.n3 = st.n3;
+  for (int mu = 0; mu < 3; ++mu) {
+    a.ih2[mu] = st.ih2[mu];
+    a.cadv[mu] = st.cadv[mu];
+    a.neu[mu] = st.neu[mu];
+  }
+  a.lam_amax = st.lam_amax;
+  a.r0 = st.r0;
+  a.r1 = st.r1;
+  a.r2 = st.r2;
+  a.r3 = st.r3;
+  a.flag = st.flag;
+  a.nondiv = st.nondiv;
+  return a;
+}
+
+// vector v of a: base u + c s, multiplied by the factors of exponential j, into out
+void slab_vector(SlabArgs& a, const mm_op* op, int v, int base, double c, int j, double* out) {
+  a.base[v] = base;
+  a.c[v] = c;
+  a.E1[v] = factor(op, 0, j);
+  a.E2[v] = factor(op, 1, j);
+  a.out[v] = out;
+}
+
+hipError_t slab(mm_ctx* ctx, const SlabArgs& a, int nvec, hipStream_t s) {
+  const double dof = (double)a.n1 * a.n2 * a.n3;
+  return timed_launch(ctx, MM_KIND_FUSED, 2.0 * (a.n1 + a.n2) * dof * nvec, s,
+                      [&] { return launch_slab(a, nvec, s); });
+}
+
+// Products along x3 that follow a slab launch: group i takes in[i] with the factor of
+// exponential j[i] to out[i] (+ add)
+hipError_t slab_last(const mm_op* op, const int* j, int groups, const double* const* in, double* const* out,
+                     const double* add, hipStream_t s) {
+  const int n = op->n[2], P = (int)(op->dof / n);
+  GemmArgs g{};
+  for (int i = 0; i < groups; ++i) {
+    g.A[i] = factor_op(op, 2, j[i]);
+    g.Ff[i] = folded(op, 2, j[i]);
+    g.B[i] = in[i];
+    g.C[i] = out[i];
+    g.Cadd[i] = add;
+  }
+  g.M = g.K = g.lda = n;
+  g.N = g.ldb = g.ldc = P;
+  g.inner = 1;
+  g.groups = groups;
+  g.b_trans = 1;
+  g.alpha = 1.0;
+  g.beta = add ? 1.0 : 0.0;
+  set_fold(op, g, 2, PassIO{});
+  return gemm(op, g, s);
+}
+
+mm_status enqueue_lawson_slab(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
+  const double tau = op->tau;
+  const int64_t dof = op->dof;
+  double *b0 = op->buf[0], *b1 = op->buf[1];
+  const double* const in[2] = {b1, b1 + dof};
+  for (int it = 0; it < nsteps; ++it) {
+    if (op->scheme == MM_SLE) {
+      // u+ = u + e^{tau A} tau F(u)
+      SlabArgs a = slab_args(op, u, true);
+      slab_vector(a, op, 0, 0, tau, 0, b1);
+      HIPCHK(ctx, slab(ctx, a, 1, s));
+      const int j[1] = {0};
+      double* const out[1] = {u};
+      HIPCHK(ctx, slab_last(op, j, 1, in, out, u, s));
+      continue;
+    }
+    // L2a: U = e^{tau/2 A}(u + tau/2 g(u)), W = e^{tau A} u; u+ = W + e^{tau/2 A} tau g(U).
+    // SL2: U = u + e^{alpha tau A} alpha tau F(u), W = u + e^{tau/2 A} tau F(u);
+    // u+ = W + e^{tau A} tau/(2 alpha) (g(U) - g(u))
+    const bool sl2 = op->scheme == MM_SL2;
+    double *U = b0, *W = b0 + dof, *g0 = op->buf[2];
+    SlabArgs a = slab_args(op, u, sl2);
+    int j[2] = {1, 0};
+    if (sl2) {
+      j[0] = 2;
+      j[1] = 1;
+      slab_vector(a, op, 0, 0, kAlphaSL2 * tau, j[0], b1);
+      slab_vector(a, op, 1, 0, tau, j[1], b1 + dof);
+      const StencilArgs g = stencil_args(op, u, false);
+      a.raw = g0;
+      a.raw_lam_amax = g.lam_amax;
+      for (int mu = 0; mu < 3; ++mu) a.raw_cadv[mu] = g.cadv[mu];
+    } else {
+      slab_vector(a, op, 0, 1, 0.5 * tau, j[0], b1);
+      slab_vector(a, op, 1, 1, 0.0, j[1], b1 + dof);
+    }
+    HIPCHK(ctx, slab(ctx, a, 2, s));
+    double* const stage[2] = {U, W};
+    HIPCHK(ctx, slab_last(op, j, 2, in, stage, sl2 ? u : nullptr, s));
+    SlabArgs b = slab_args(op, U, false);
+    b.sub = sl2 ? g0 : nullptr;
+    j[0] = sl2 ? 0 : 1;
+    slab_vector(b, op, 0, 0, sl2 ? 0.5 * tau / kAlphaSL2 : tau, j[0], b1);
+    HIPCHK(ctx, slab(ctx, b, 1, s));
+    double* const out[1] = {u};
+    HIPCHK(ctx, slab_last(op, j, 1, in, out, W, s));
+  }
+  return MM_OK;
+}
+
 // Enqueue nsteps Lawson steps on s (arguments already validated).
 mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
   const double tau = op->tau;
@@ -1898,6 +2025,7 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
   double* b0 = op->buf[0];
   double* b1 = op->buf[1];
   const bool mixed = lowp(op);
+  if (slab_active(op)) return enqueue_lawson_slab(ctx, op, u, nsteps, s);
   // (the one-workgroup solver implements the flux form with Dirichlet data only)
   if (ctx->small_fused && op->prec == MM_FP64 && small2d_fits(op->d, op->n[0], op->n[1]) &&
       op->form == MM_FORM_FLUX && op->bc[0] == MM_BC_DIRICHLET && op->bc[1] == MM_BC_DIRICHLET &&

@@ -1030,6 +1030,7 @@ hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s) {
     const int ldf = g.b_trans ? g.lda : g.ldb;
     if (ldf < fac_ld(g.K) || ldf % kFacPad != 0) return hipErrorInvalidValue;
   }
+  if (prec == MM_FP64 && g.tile == 0 && plain_regs_fits(g)) return launch_plain_regs(g, s);
   switch (choose_tile(g, prec)) {
     case 32: return launch_tile<32>(prec, g, s);
     case 64: return launch_tile<64>(prec, g, s);

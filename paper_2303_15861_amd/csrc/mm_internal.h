@@ -158,6 +158,31 @@ struct SmallBatch {
 };
 hipError_t launch_lawson_small2d_batch(const SmallArgs* a, int count, bool l2b, hipStream_t s);
 
+// Stage vectors and their first two mode products, slab by slab (slab.hip; FP64, d = 3, n1 and
+// n2 at most 64, unpadded rows): out[v] = E1[v] x_1 E2[v] x_2 (base[v] u + c[v] (s - sub)) with s
+// the remainder stencil of the given coefficients (see StencilArgs); c[v] = 0: of u itself.
+// raw (nullable): also the stencil of the raw_ coefficients, without sub.
+struct SlabArgs {
+  const double* u;
+  const double* a;
+  int n1, n2, n3;
+  double ih2[3], cadv[3], lam_amax;
+  double r0, r1, r2, r3;
+  const double* sub;
+  int* flag;            // nullable: set to 1 if a stage value is not finite
+  int neu[3];
+  int nondiv;
+  int base[2];          // 0 or 1
+  double c[2];
+  const double* E1[2];
+  const double* E2[2];
+  double* out[2];
+  double* raw;
+  double raw_lam_amax, raw_cadv[3];
+};
+bool slab_fits(int d, int n1, int n2, int n3);
+hipError_t launch_slab(const SlabArgs& a, int nvec, hipStream_t s);   // nvec: 1 or 2
+
 hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s);
 // Row stride of a folded factor: f = n - n/2 rounded up to even (16-byte aligned pairs).
 __host__ __device__ inline int fold_ld(int n) {
@@ -185,6 +210,9 @@ int64_t fold_tiles(const GemmArgs& g);
 // (32-bit byte offsets).
 bool fold_regs_fits(const GemmArgs& g);
 hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s);
+// Plain FP64 products of the same kind, square factors of at most 64 points.
+bool plain_regs_fits(const GemmArgs& g);
+hipError_t launch_plain_regs(GemmArgs& g, hipStream_t s);
 // Tile size the launcher takes for g in precision prec (g.tile if set, else 64 when
 // 128-tiles would not fill the chip once, and in FP64 32 when 64-tiles would not give
 // every compute unit one).

@@ -51,6 +51,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand(const void* base) {
 __device__ __forceinline__ d2 load2(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform) {
   return __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(r, off, uniform, 0));
 }
+__device__ __forceinline__ double load1(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, uniform, 0));
+}
 __device__ __forceinline__ void store1(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, uniform, 2 /* nontemporal */);
 }
@@ -158,7 +161,7 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
   const unsigned kb = 2u * (unsigned)tk * ks;
   // (mode 1: the pair x[n-2-k], x[n-1-k])
   const unsigned mb = (unsigned)(n - (BT ? 1 : 2) - DK) * ks - kb;
-  const __amdgpu_buffer_rsrc_t xr = operand(X), cr = operand(C);
+  const __amdgpu_buffer_rsrc_t xr = operand(X), cr = operand(C), ar = operand(Cadd);
   unsigned foff = 0;   // modes 2/3: offset of the thread's columns in the tile being loaded
   auto position = [&]() {
     if (BT) {
@@ -290,21 +293,29 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
     store1(cr, lane0(j, t), rb[j] + t * st, FOLD ? a + b : a);
     if (FOLD) store1(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, a - b);
   };
-  // the tile's results with alpha and the added term
+  // the tile's results with alpha and the added term (all its loads in flight together; a load
+  // at kOut gives zero)
   auto write_scaled = [&]() {
     const double alpha = p.alpha, beta = p.beta;
+    double x[NC][4][NS];
 #pragma unroll
     for (int j = 0; j < NC; ++j)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        auto put = [&](unsigned off, unsigned du, double v) {
-          v *= alpha;
-          if (Cadd && off != kOut) v += beta * *(const double*)((const char*)Cadd + ((int64_t)off + du));
-          store1(cr, off, du, v);
-        };
+        x[j][t][0] = x[j][t][NS - 1] = 0.0;
+        if (Cadd) {
+          x[j][t][0] = load1(ar, lane0(j, t), rb[j] + t * st);
+          if (FOLD) x[j][t][NS - 1] = load1(ar, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st);
+        }
+      }
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
         const double a = acc[0][j][t], b = FOLD ? acc[NS - 1][j][t] : 0.0;
-        put(lane0(j, t), rb[j] + t * st, FOLD ? a + b : a);
-        if (FOLD) put(lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, a - b);
+        const double y0 = alpha * (FOLD ? a + b : a), y1 = alpha * (a - b);
+        store1(cr, lane0(j, t), rb[j] + t * st, Cadd ? y0 + beta * x[j][t][0] : y0);
+        if (FOLD) store1(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, Cadd ? y1 + beta * x[j][t][NS - 1] : y1);
       }
   };
 
@@ -331,9 +342,11 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
           const d2 v = k < ldf ? *reinterpret_cast<const d2*>(src + k) : d2{0.0, 0.0};
           F[q][2 * h] = v.x;
           F[q][2 * h + 1] = v.y;
-        } else {
-          F[q][2 * h] = k < n ? src[k] : 0.0;
-          F[q][2 * h + 1] = k + 1 < n ? src[k + 1] : 0.0;
+        } else {   // (pairs past the row are clamped into the factor, its last pair one back)
+          const int64_t i = (int64_t)row * ldf + k, last = (int64_t)(rows - 1) * ldf + n - 2, c = i < last ? i : last;
+          const d2 v = *reinterpret_cast<const d2u*>(Fq + c);
+          F[q][2 * h] = k < n ? (c == i ? v.x : v.y) : 0.0;
+          F[q][2 * h + 1] = k + 1 < n ? v.y : 0.0;
         }
       }
     __builtin_amdgcn_sched_barrier(0);
@@ -455,8 +468,8 @@ struct Shape {
   static constexpr int RT = (H + 1) / 2;   // row tiles of a square factor (folded: of f <= 8H)
   static constexpr int RW = RT > 8 ? 4 : RT;
   static constexpr int WC = RT == 1 ? 4 : RT == 2 || RT == 5 || RT == 6 ? 2 : 1;
-  static constexpr int NC = RT == 3 || RT == 4 ? 2 : 1;
-  static constexpr int WPE = RT > 8 ? 1 : RT >= 7 || RT == 4 ? 2 : RT >= 3 ? 3 : 4;
+  static constexpr int NC = FOLD && (RT == 3 || RT == 4) ? 2 : 1;
+  static constexpr int WPE = !FOLD ? 4 : RT > 8 ? 1 : RT >= 7 || RT == 4 ? 2 : RT >= 3 ? 3 : 4;
   static constexpr int LATE = RT >= 5 && RT <= 8;
 };
 
@@ -524,6 +537,41 @@ hipError_t launch_fold_bt(GemmArgs& g, hipStream_t s) {
 
 }  // namespace
 
+namespace {
+
+// 32-bit byte offsets of the grid operands
+bool offsets_fit(const GemmArgs& g) {
+  const int64_t lim = (int64_t)1 << 28;   // values
+  const int64_t in = g.b_trans ? (g.inner - 1) * g.sB + (int64_t)g.K * g.ldb : (int64_t)g.M * g.lda;
+  const int64_t out = g.b_trans ? (g.inner - 1) * g.sC + (int64_t)g.M * g.ldc : (int64_t)g.M * g.ldc;
+  return in < lim && out < lim;
+}
+
+template <int BT>
+hipError_t launch_plain_bt(GemmArgs& g, hipStream_t s) {
+  switch ((g.K + 15) / 16) {
+    case 1:
+    case 2: return launch_regs_h<BT, 0, 4>(g, s);
+    case 3: return launch_regs_h<BT, 0, 6>(g, s);
+    case 4: return launch_regs_h<BT, 0, 8>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+// Plain products of square factors of 2 to 64 points: the tiled kernel walks a serial chain of
+// K chunks, each with its load latency on a launch this small; here all of K is loaded at
+// once.
+bool plain_regs_fits(const GemmArgs& g) {
+  return g.fold_blocks <= 1 && g.K >= 2 && g.K <= 64 && (g.b_trans ? g.M : g.N) == g.K && (!g.b_trans || g.N >= 2) &&
+         g.sA == 0 && !g.in_f32 && !g.out_f32 && offsets_fit(g);
+}
+
+hipError_t launch_plain_regs(GemmArgs& g, hipStream_t s) {
+  return g.b_trans ? launch_plain_bt<1>(g, s) : launch_plain_bt<0>(g, s);
+}
+
 // Up to 128 folded positions the register-held kernel is the faster one at every size. Beyond,
 // with one wave per SIMD, it wins where the tiled kernel's 128 x 64 tiles do not fill the
 // chip (512 of them): two 511 x 511 vectors 14.5 us per product against 22-24 (plain
@@ -535,10 +583,7 @@ bool fold_regs_fits(const GemmArgs& g) {
   const int n = g.K;
   if (g.fold_blocks > 1 || n < 17 || n > 512 || (g.b_trans && g.N < 2)) return false;
   if (n > 256 && fold_tiles(g) >= kWideMaxTiles) return false;
-  const int64_t lim = (int64_t)1 << 28;   // values
-  const int64_t in = g.b_trans ? (g.inner - 1) * g.sB + (int64_t)n * g.ldb : (int64_t)g.M * g.lda;
-  const int64_t out = g.b_trans ? (g.inner - 1) * g.sC + (int64_t)n * g.ldc : (int64_t)g.M * g.ldc;
-  return in < lim && out < lim;
+  return offsets_fit(g);
 }
 
 hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s) { return g.b_trans ? launch_fold_bt<1>(g, s) : launch_fold_bt<0>(g, s); }
