@@ -2018,6 +2018,148 @@ mm_status enqueue_lawson_slab(mm_ctx* ctx, const mm_op* op, double* u, int nstep
   return MM_OK;
 }
 
+// Lawson steps of small periodic 2D problems as launches of independent product tasks
+// (periodic.hip): FP64, flux form, axes of at most 256 points. The remainder's two axes, the
+// operator's part of F and independent actions share launches, every pointwise pass is an
+// epilogue: a step of the stabilised Lawson2 has eight launches on one stream instead of
+// forty on two (256^2, Sec. 5.1: 261 -> 60 us).
+bool periodic_active(const mm_op* op) {
+  return op->periodic && op->prec == MM_FP64 && op->form == MM_FORM_FLUX && periodic_fits(op->d, op->n[0], op->n[1]);
+}
+
+hipError_t periodic_tasks(const mm_op* op, const PeriodicTask* t, int count, hipStream_t s) {
+  double work = 0.0;
+  for (int i = 0; i < count; ++i)
+    for (int q = 0; q < 2; ++q)
+      if (t[i].M[q]) work += 2.0 * (double)op->dof * op->n[t[i].mode[q]];
+  return timed_launch(op->ctx, MM_KIND_FUSED, work, s,
+                      [&] { return launch_periodic(t, count, op->n[0], op->n[1], s); });
+}
+
+// out = c (M x_mu X) + base
+PeriodicTask product_task(const double* M, int mu, const double* X, double* out, double c, const double* base) {
+  PeriodicTask t{};
+  t.M[0] = M;
+  t.X[0] = X;
+  t.mode[0] = mu;
+  t.scale = 1.0;
+  t.c[0] = c;
+  t.base[0] = base;
+  t.out[0] = out;
+  return t;
+}
+
+// the fluxes T_mu = (a_mu - lam a_max,mu) D_mu u + (b_mu - beta_bar_mu) u of both axes, and, for
+// F, H = A u
+hipError_t periodic_fluxes(const mm_op* op, const double* u, double* const* T, double* H, hipStream_t s) {
+  PeriodicTask t[3];
+  for (int mu = 0; mu < 2; ++mu) {
+    t[mu] = product_task(op->dmat[mu], mu, u, T[mu], 1.0, nullptr);
+    t[mu].coef = op->a + mu * op->dof;
+    t[mu].coef0 = op->lam * op->amax_mu[mu];
+    t[mu].flux_u = u;
+    t[mu].vel = op->vel ? op->vel + mu * op->dof : nullptr;
+    t[mu].vel_const = op->beta[mu];
+    t[mu].vel0 = op->beta_bar[mu];
+  }
+  if (H) {
+    const int64_t n0 = op->n[0], n1 = op->n[1];
+    t[2] = product_task(op->dmat[0] + 2 * n0 * n0, 0, u, H, 1.0, nullptr);
+    t[2].M[1] = op->dmat[1] + 2 * n1 * n1;
+    t[2].X[1] = u;
+    t[2].mode[1] = 1;
+  }
+  return periodic_tasks(op, t, H ? 3 : 2, s);
+}
+
+// g = r(u) + D_1 T_1 + D_2 T_2, as stage outputs c g + base (set by the caller)
+PeriodicTask remainder_task(const mm_op* op, const double* u, double* const* T) {
+  PeriodicTask t = product_task(op->dmat[0], 0, T[0], nullptr, 1.0, nullptr);
+  t.M[1] = op->dmat[1];
+  t.X[1] = T[1];
+  t.mode[1] = 1;
+  t.react = u;
+  for (int i = 0; i < 4; ++i) t.r[i] = op->r[i];
+  t.flag = op->flag;
+  return t;
+}
+
+mm_status enqueue_lawson_periodic(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
+  const double tau = op->tau;
+  const int64_t dof = op->dof;
+  double* const T[2] = {op->spec_ws, op->spec_ws + dof};
+  double *H = op->spec_ws + 2 * dof, *P = op->spec_ws + 3 * dof, *P2 = op->spec_ws + 4 * dof;
+  double *v = op->buf[0], *v2 = op->buf[0] + dof, *U = op->buf[1], *W = op->buf[1] + dof;
+  auto E = [&](int mu, int j) { return factor(op, mu, j); };
+  PeriodicTask t[2];
+  for (int it = 0; it < nsteps; ++it) {
+    const int sch = op->scheme;
+    const bool full = sch == MM_SLE || sch == MM_SL2;
+    // stage one: v (and v2) from g(u) or F(u) = g(u) + H
+    HIPCHK(ctx, periodic_fluxes(op, u, T, full ? H : nullptr, s));
+    t[0] = remainder_task(op, u, T);
+    if (sch == MM_SL2) {          // v = F, v2 = g
+      t[0].base[0] = H;
+      t[0].out[0] = v;
+      t[0].out[1] = v2;
+      t[0].c[1] = 1.0;
+    } else if (sch == MM_SLE) {   // v = F
+      t[0].base[0] = H;
+      t[0].out[0] = v;
+    } else {                      // v = u + tau g (L2a: tau/2), L2b: v2 = u + tau/2 g
+      t[0].base[0] = u;
+      t[0].c[0] = sch == MM_LAWSON2A ? 0.5 * tau : tau;
+      t[0].out[0] = v;
+      if (sch == MM_LAWSON2B) {
+        t[0].base[1] = u;
+        t[0].c[1] = 0.5 * tau;
+        t[0].out[1] = v2;
+      }
+    }
+    HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+    if (sch == MM_LAWSON_EULER || sch == MM_SLE) {
+      // u+ = e^{tau A} v, or u + tau e^{tau A} v
+      t[0] = product_task(E(0, 0), 0, v, P, 1.0, nullptr);
+      HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+      t[0] = product_task(E(1, 0), 1, P, u, sch == MM_SLE ? tau : 1.0, sch == MM_SLE ? u : nullptr);
+      HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+      continue;
+    }
+    // the step's two actions of stage one: U, and W, to which the last action is added
+    //   L2a: U = e^{tau/2 A} v, W = e^{tau A} u;  L2b: [U, W] = e^{tau A}[v, v2]
+    //   SL2: U = u + alpha tau e^{alpha tau A} F, W = u + tau e^{tau/2 A} F
+    const int jU = sch == MM_SL2 ? 2 : sch == MM_LAWSON2A ? 1 : 0, jW = sch == MM_SL2 ? 1 : 0;
+    const double* inW = sch == MM_SL2 ? v : sch == MM_LAWSON2A ? u : v2;
+    t[0] = product_task(E(0, jU), 0, v, P, 1.0, nullptr);
+    t[1] = product_task(E(0, jW), 0, inW, P2, 1.0, nullptr);
+    HIPCHK(ctx, periodic_tasks(op, t, 2, s));
+    const double* base = sch == MM_SL2 ? u : nullptr;
+    t[0] = product_task(E(1, jU), 1, P, U, sch == MM_SL2 ? kAlphaSL2 * tau : 1.0, base);
+    t[1] = product_task(E(1, jW), 1, P2, W, sch == MM_SL2 ? tau : 1.0, base);
+    HIPCHK(ctx, periodic_tasks(op, t, 2, s));
+    // stage two
+    HIPCHK(ctx, periodic_fluxes(op, U, T, nullptr, s));
+    t[0] = remainder_task(op, U, T);
+    if (sch == MM_LAWSON2B) {     // u+ = W + tau/2 g(U)
+      t[0].base[0] = W;
+      t[0].c[0] = 0.5 * tau;
+      t[0].out[0] = u;
+      HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+      continue;
+    }
+    // L2a: u+ = W + tau e^{tau/2 A} g(U); SL2: u+ = W + tau/(2 alpha) e^{tau A}(g(U) - g(u))
+    t[0].sub = sch == MM_SL2 ? v2 : nullptr;
+    t[0].out[0] = v;
+    HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+    const int j = sch == MM_SL2 ? 0 : 1;
+    t[0] = product_task(E(0, j), 0, v, P, 1.0, nullptr);
+    HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+    t[0] = product_task(E(1, j), 1, P, u, sch == MM_SL2 ? 0.5 * tau / kAlphaSL2 : tau, W);
+    HIPCHK(ctx, periodic_tasks(op, t, 1, s));
+  }
+  return MM_OK;
+}
+
 // Enqueue nsteps Lawson steps on s (arguments already validated).
 mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
   const double tau = op->tau;
@@ -2026,6 +2168,7 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
   double* b1 = op->buf[1];
   const bool mixed = lowp(op);
   if (slab_active(op)) return enqueue_lawson_slab(ctx, op, u, nsteps, s);
+  if (periodic_active(op)) return enqueue_lawson_periodic(ctx, op, u, nsteps, s);
   // (the one-workgroup solver implements the flux form with Dirichlet data only)
   if (ctx->small_fused && op->prec == MM_FP64 && small2d_fits(op->d, op->n[0], op->n[1]) &&
       op->form == MM_FORM_FLUX && op->bc[0] == MM_BC_DIRICHLET && op->bc[1] == MM_BC_DIRICHLET &&

@@ -137,6 +137,38 @@ struct SpecMidArgs {
   int nondiv;
 };
 
+// One task of a launch of small periodic 2D products (periodic.hip): with acc = sum_q M[q] x X[q]
+// (mode 0: along x1, 1: along x2; M[1] null: one product),
+//   g = S acc + flux_u (v - vel0) + r(react) - sub,  S = coef - coef0 or scale, v = vel or vel_const
+//   out[i] = base[i] + c[i] g
+// (nullable: coef, flux_u, vel, react, sub, base[i], out[1], flag). Outputs may not be inputs
+// of a product of the same launch.
+struct PeriodicTask {
+  const double* M[2];
+  const double* X[2];
+  int mode[2];
+  double scale;
+  const double* coef;
+  double coef0;
+  const double* flux_u;
+  const double* vel;
+  double vel_const, vel0;
+  const double* react;
+  double r[4];
+  const double* sub;
+  const double* base[2];
+  double c[2];
+  double* out[2];
+  int* flag;
+};
+constexpr int kMaxPeriodicTasks = 3;
+struct PeriodicBatch {
+  PeriodicTask t[kMaxPeriodicTasks];
+  int n1, n2;
+};
+bool periodic_fits(int d, int n1, int n2);
+hipError_t launch_periodic(const PeriodicTask* t, int count, int n1, int n2, hipStream_t s);
+
 // Whole small 2D Lawson solves in one workgroup (n1, n2 <= 64, FP64).
 struct SmallArgs {
   double* u;            // n2 x n1, advanced in place
