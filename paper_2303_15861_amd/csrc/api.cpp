@@ -2160,6 +2160,42 @@ mm_status enqueue_lawson_periodic(mm_ctx* ctx, const mm_op* op, double* u, int n
   return MM_OK;
 }
 
+// nsteps Lawson steps of a small 2D problem for the one-workgroup solver: with folded factors
+// where both axes have them
+SmallArgs small_args(const mm_op* op, double* u, int nsteps) {
+  const StencilArgs sa = stencil_args(op, u, false);
+  SmallArgs a{};
+  a.u = u;
+  a.a = op->a;
+  a.E1 = factor(op, 0, 0);
+  a.E2 = factor(op, 1, 0);
+  if ((!op->ctx || op->ctx->fold != 0) && folded(op, 0, 0) && folded(op, 1, 0)) {
+    a.Ef1 = folded(op, 0, 0);
+    a.Ef2 = folded(op, 1, 0);
+  }
+  a.n1 = op->n[0];
+  a.n2 = op->n[1];
+  a.nsteps = nsteps;
+  a.tau = op->tau;
+  for (int mu = 0; mu < 2; ++mu) {
+    a.ih2[mu] = sa.ih2[mu];
+    a.cadv[mu] = sa.cadv[mu];
+  }
+  a.lam_amax = sa.lam_amax;
+  a.r0 = sa.r0;
+  a.r1 = sa.r1;
+  a.r2 = sa.r2;
+  a.r3 = sa.r3;
+  a.flag = op->flag;
+  return a;
+}
+
+// floating-point operations of its mode products
+double small_work(const mm_op* op, const SmallArgs& a) {
+  return (double)a.nsteps * (op->scheme == MM_LAWSON2B ? 2 : 1) * (a.Ef1 ? 1.0 : 2.0) * (double)op->dof *
+         (op->n[0] + op->n[1]);
+}
+
 // Enqueue nsteps Lawson steps on s (arguments already validated).
 mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
   const double tau = op->tau;
@@ -2175,28 +2211,8 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
       (op->scheme == MM_LAWSON_EULER || op->scheme == MM_LAWSON2B)) {
     // the whole time loop in one workgroup
     if (nsteps == 0) return MM_OK;
-    const StencilArgs sa = stencil_args(op, u, false);
-    SmallArgs a{};
-    a.u = u;
-    a.a = op->a;
-    a.E1 = factor(op, 0, 0);
-    a.E2 = factor(op, 1, 0);
-    a.n1 = op->n[0];
-    a.n2 = op->n[1];
-    a.nsteps = nsteps;
-    a.tau = tau;
-    for (int mu = 0; mu < 2; ++mu) {
-      a.ih2[mu] = sa.ih2[mu];
-      a.cadv[mu] = sa.cadv[mu];
-    }
-    a.lam_amax = sa.lam_amax;
-    a.r0 = sa.r0;
-    a.r1 = sa.r1;
-    a.r2 = sa.r2;
-    a.r3 = sa.r3;
-    a.flag = op->flag;
-    const double work = (double)nsteps * (op->scheme == MM_LAWSON2B ? 2 : 1) * 2.0 *
-                        (double)op->dof * (op->n[0] + op->n[1]);
+    const SmallArgs a = small_args(op, u, nsteps);
+    const double work = small_work(op, a);
     HIPCHK(ctx, timed_launch(ctx, MM_KIND_FUSED, work, s,
                              [&] { return launch_lawson_small2d(a, op->scheme == MM_LAWSON2B, s); }));
     return MM_OK;
@@ -2769,28 +2785,8 @@ mm_status enqueue_small2d_group(mm_ctx* ctx, const mm_op* const* ops, double* co
   for (int i = 0; i < count; ++i) {
     const mm_op* op = ops[i];
     if ((op->scheme == MM_LAWSON2B) != l2b) return MM_EINVAL;
-    const StencilArgs sa = stencil_args(op, u[i], false);
-    SmallArgs& a = args[i];
-    a = SmallArgs{};
-    a.u = u[i];
-    a.a = op->a;
-    a.E1 = factor(op, 0, 0);
-    a.E2 = factor(op, 1, 0);
-    a.n1 = op->n[0];
-    a.n2 = op->n[1];
-    a.nsteps = nsteps[i];
-    a.tau = op->tau;
-    for (int mu = 0; mu < 2; ++mu) {
-      a.ih2[mu] = sa.ih2[mu];
-      a.cadv[mu] = sa.cadv[mu];
-    }
-    a.lam_amax = sa.lam_amax;
-    a.r0 = sa.r0;
-    a.r1 = sa.r1;
-    a.r2 = sa.r2;
-    a.r3 = sa.r3;
-    a.flag = op->flag;
-    work += (double)nsteps[i] * (l2b ? 2 : 1) * 2.0 * (double)op->dof * (op->n[0] + op->n[1]);
+    args[i] = small_args(op, u[i], nsteps[i]);
+    work += small_work(op, args[i]);
   }
   HIPCHK(ctx, timed_launch(ctx, MM_KIND_FUSED, work, s,
                            [&] { return launch_lawson_small2d_batch(args, count, l2b, s); }));

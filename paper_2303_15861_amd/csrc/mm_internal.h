@@ -175,6 +175,8 @@ struct SmallArgs {
   const double* a;      // (n2+2) x (n1+2)
   const double* E1;     // n1 x n1 factor exp(tau A_1)
   const double* E2;     // n2 x n2 factor exp(tau A_2)
+  const double* Ef1;    // both in folded form (launch_fold_factor), or both null: plain products
+  const double* Ef2;
   int n1, n2, nsteps;
   double tau;
   double ih2[2], cadv[2], lam_amax;
