@@ -2196,6 +2196,24 @@ double small_work(const mm_op* op, const SmallArgs& a) {
          (op->n[0] + op->n[1]);
 }
 
+// The end of a Lawson2b step on the transformed pair [U, W] = res and the start of the next into
+// v (both padded): u+ = W + tau/2 g(U), v1 = u+ + tau g(u+), v2 = u+ + tau/2 g(u+).
+StencilArgs lawson2b_pair(const mm_op* op, const double* res, double* v) {
+  StencilArgs a = stencil_args(op, res, false);
+  a.base0 = res + op->dofp;
+  a.c0 = 0.5 * op->tau;
+  a.c1 = op->tau;
+  a.ldi = a.ldo = op->ld1;
+  a.out0 = v;
+  a.out1 = v + op->dofp;
+  return a;
+}
+// whether the two run as one launch (bit for bit the two launches), for count such problems
+bool lawson2b_pairs(const mm_op* op, const double* res, double* v, int count) {
+  return op->scheme == MM_LAWSON2B && op->prec == MM_FP64 && res != v &&
+         stencil_pair_pays(op->d, lawson2b_pair(op, res, v), count);
+}
+
 // Enqueue nsteps Lawson steps on s (arguments already validated).
 mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipStream_t s) {
   const double tau = op->tau;
@@ -2217,6 +2235,7 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
                              [&] { return launch_lawson_small2d(a, op->scheme == MM_LAWSON2B, s); }));
     return MM_OK;
   }
+  const bool pair = nsteps > 1 && lawson2b_pairs(op, op->d == 3 ? b1 : b0, b0, 1);
   for (int it = 0; it < nsteps; ++it) {
     if (op->scheme == MM_LAWSON_EULER) {
       // u+ = e^{tau A}(u + tau g(u)); the stage vector in the padded layout
@@ -2279,30 +2298,38 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
       // v1 = u + tau g(u), v2 = u + tau/2 g(u); [U, W] = e^{tau A}[v1, v2]; u+ = W + tau/2 g(U)
       // (v1, v2, U, W in the padded layout: rows of ld1, dofp apart)
       const int64_t dp = op->dofp;
-      StencilArgs a = stencil_args(op, u, false);
-      a.base0 = u;
-      a.c0 = tau;
-      a.base1 = u;
-      a.c1 = 0.5 * tau;
-      a.ldo = op->ld1;
-      const bool dg = stencil_digits(op);
-      if (dg) {
-        set_stencil_digits(a, op, op->vdig, op->vexp, 2);
-        a.dchain = chain_active(op);
-      } else if (mixed) {
-        a.out0f = (float*)b0;
-        a.out1f = (float*)b0 + dp;
-      } else {
-        a.out0 = b0;
-        a.out1 = b0 + dp;
-      }
-      HIPCHK(ctx, stencil(op, a, s));
       double* res = (op->d == 3) ? b1 : b0;
+      const bool dg = stencil_digits(op);
+      if (it == 0 || !pair) {
+        StencilArgs a = stencil_args(op, u, false);
+        a.base0 = u;
+        a.c0 = tau;
+        a.base1 = u;
+        a.c1 = 0.5 * tau;
+        a.ldo = op->ld1;
+        if (dg) {
+          set_stencil_digits(a, op, op->vdig, op->vexp, 2);
+          a.dchain = chain_active(op);
+        } else if (mixed) {
+          a.out0f = (float*)b0;
+          a.out1f = (float*)b0 + dp;
+        } else {
+          a.out0 = b0;
+          a.out1 = b0 + dp;
+        }
+        HIPCHK(ctx, stencil(op, a, s));
+      }
       if (dg && chain_active(op))
         HIPCHK(ctx, chain_action(op, 0, 2, res, staged(op), s));
       else
         HIPCHK(ctx, exp_action(op, 0, b0, mixed, res, 2, b1, b0, s, nullptr, 1.0, 1.0, staged(op), staged(op),
                                staged(op), dg));
+      if (pair && it + 1 < nsteps) {
+        const StencilArgs c = lawson2b_pair(op, res, b0);
+        HIPCHK(ctx, timed_launch(ctx, MM_KIND_STENCIL, 2.0 * (double)dof, s,
+                                 [&] { return launch_stencil_pair(&c, 1, s); }));
+        continue;
+      }
       StencilArgs c = stencil_args(op, res, false);
       c.base0 = res + dp;
       c.c0 = 0.5 * tau;
@@ -2717,33 +2744,38 @@ mm_status enqueue_lawson_group(mm_ctx* ctx, const mm_op* const* ops, double* con
   // problem's slot of the group workspace (group i at i S plane bytes, i F exponents)
   const bool dg = stencil_digits(o0);
   const int64_t fib1 = (int64_t)nvec * (dof / o0->n[0]);
+  bool pair = l2b && nsteps > 1;
+  for (int i = 0; i < count; ++i)
+    pair = pair && lawson2b_pairs(ops[i], (const double*)out[i], ops[i]->buf[0], count);
   for (int it = 0; it < nsteps; ++it) {
-    // v1 = u + tau g(u) (and for Lawson2b v2 = u + tau/2 g(u)) into buf[0]
-    for (int i = 0; i < count; ++i) {
-      const mm_op* op = ops[i];
-      double* b0 = op->buf[0];
-      StencilArgs a = stencil_args(op, u[i], false);
-      a.base0 = u[i];
-      a.c0 = op->tau;
-      a.ldo = op->ld1;
-      if (l2b) {
-        a.base1 = u[i];
-        a.c1 = 0.5 * op->tau;
+    if (it == 0 || !pair) {
+      // v1 = u + tau g(u) (and for Lawson2b v2 = u + tau/2 g(u)) into buf[0]
+      for (int i = 0; i < count; ++i) {
+        const mm_op* op = ops[i];
+        double* b0 = op->buf[0];
+        StencilArgs a = stencil_args(op, u[i], false);
+        a.base0 = u[i];
+        a.c0 = op->tau;
+        a.ldo = op->ld1;
+        if (l2b) {
+          a.base1 = u[i];
+          a.c1 = 0.5 * op->tau;
+        }
+        if (dg) {
+          set_stencil_digits(a, op, ws->vdig + (int64_t)i * o0->slices * fib1 * slice_ld(o0->n[0]), ws->vexp + i * fib1,
+                             nvec);
+        } else if (mixed) {
+          a.out0f = (float*)b0;
+          if (l2b) a.out1f = (float*)b0 + dp;
+        } else {
+          a.out0 = b0;
+          if (l2b) a.out1 = b0 + dp;
+        }
+        sa[i] = a;
       }
-      if (dg) {
-        set_stencil_digits(a, op, ws->vdig + (int64_t)i * o0->slices * fib1 * slice_ld(o0->n[0]), ws->vexp + i * fib1,
-                           nvec);
-      } else if (mixed) {
-        a.out0f = (float*)b0;
-        if (l2b) a.out1f = (float*)b0 + dp;
-      } else {
-        a.out0 = b0;
-        if (l2b) a.out1 = b0 + dp;
-      }
-      sa[i] = a;
+      HIPCHK(ctx, timed_launch(ctx, MM_KIND_STENCIL, (double)dof * count, s,
+                               [&] { return launch_stencil_batch(d, sa, count, s); }));
     }
-    HIPCHK(ctx, timed_launch(ctx, MM_KIND_STENCIL, (double)dof * count, s,
-                             [&] { return launch_stencil_batch(d, sa, count, s); }));
     // e^{tau A}: buf[0] -> buf[1] (-> buf[0]) -> out, stage vectors padded
     const Layout lp = staged(o0), lout = l2b ? lp : natural(o0);
     HIPCHK(ctx, group_pass(ctx, ops, count, 0, nvec, in, t0, PassIO{mixed, mixed, dg}, ws, s, lp, lp));
@@ -2757,6 +2789,12 @@ mm_status enqueue_lawson_group(mm_ctx* ctx, const mm_op* const* ops, double* con
                              lp, lout));
     }
     if (!l2b) continue;
+    if (pair && it + 1 < nsteps) {
+      for (int i = 0; i < count; ++i) sa[i] = lawson2b_pair(ops[i], (const double*)out[i], ops[i]->buf[0]);
+      HIPCHK(ctx, timed_launch(ctx, MM_KIND_STENCIL, 2.0 * (double)dof * count, s,
+                               [&] { return launch_stencil_pair(sa, count, s); }));
+      continue;
+    }
     // u+ = W + tau/2 g(U) with [U, W] the transformed pair
     for (int i = 0; i < count; ++i) {
       const mm_op* op = ops[i];

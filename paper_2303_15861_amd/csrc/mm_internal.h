@@ -292,6 +292,12 @@ hipError_t launch_stencil(int d, const StencilArgs& a, hipStream_t s);
 // count (1..kMaxGroups) problems with equal n1, n2, n3 in one launch; each problem's
 // outputs are bit-identical to launch_stencil's.
 hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStream_t s);
+// The last stage of a Lawson2b step and the first of the next at once (3D, FP64, flux form,
+// Dirichlet ends, equal row strides ldi = ldo): u+ = base0 + c0 g(u), out0 = u+ + c1 g(u+),
+// out1 = u+ + c0 g(u+); flag concerns u+. out0 and out1 overlap neither u nor base0.
+// stencil_pair_pays: whether `count` problems of this shape take it.
+bool stencil_pair_pays(int d, const StencilArgs& a, int count);
+hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s);
 hipError_t launch_build_circulant(double* M, int n, const double* col, hipStream_t s);
 hipError_t launch_spec_react(double* G, const double* u, int64_t n, const double* r, hipStream_t s);
 hipError_t launch_spec_mid(const SpecMidArgs& a, hipStream_t s);

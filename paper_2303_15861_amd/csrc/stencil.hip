@@ -11,6 +11,7 @@
 // neighbours along the axis are equal (u_{n+1} = u_{n-1}), so no extra loads.
 // The stage updates of the schemes are fused as out0 = base0 + c0 (g - sub) and
 // out1 = base1 + c1 (g - sub), so each remainder evaluation is one pass over HBM.
+#include <algorithm>
 #include <cfloat>
 
 #include "mm_internal.h"
@@ -146,6 +147,20 @@ __device__ __forceinline__ void write_row_digits(const double (&v)[P], int cnt, 
         *(base + t * pstride) = (signed char)w;
     }
   }
+}
+
+// The flux form's arithmetic, with its multiply-adds written out: stencil_body and
+// stencil_pair_kernel agree bit for bit.
+// less the extracted part, the mean of a at a face
+__device__ __forceinline__ double face(double a0, double a1, double la) { return __builtin_fma(0.5, a0 + a1, -la); }
+// v + one axis' part of g at a point (u0) between um and up, with the faces cm and cp
+__device__ __forceinline__ double flux_axis(double v, double cp, double cm, double up, double u0, double um, double ih2,
+                                            double cadv) {
+  v = __builtin_fma(__builtin_fma(cp, up - u0, -(cm * (u0 - um))), ih2, v);
+  return __builtin_fma(cadv, up - um, v);
+}
+__device__ __forceinline__ double reaction(const StencilArgs& p, double u0) {
+  return __builtin_fma(u0, __builtin_fma(u0, __builtin_fma(u0, p.r3, p.r2), p.r1), p.r0);
 }
 
 template <int D, int P, int S>
@@ -330,19 +345,16 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
           }
         } else {
           const double axm = (k == 0) ? al : ac[k - 1], axp = (k == P - 1) ? ar : ac[k + 1];
-          v = ((0.5 * (a0 + axp) - la) * (uxp - u0) - (0.5 * (a0 + axm) - la) * (u0 - uxm)) * p.ih2[0] +
-              p.cadv[0] * (uxp - uxm);
-          v += ((0.5 * (a0 + aa[y + 1][z][k]) - la) * (uyp - u0) - (0.5 * (a0 + aa[y - 1][z][k]) - la) * (u0 - uym)) *
-                   p.ih2[1] +
-               p.cadv[1] * (uyp - uym);
+          v = flux_axis(0.0, face(a0, axp, la), face(a0, axm, la), uxp, u0, uxm, p.ih2[0], p.cadv[0]);
+          v = flux_axis(v, face(a0, aa[y + 1][z][k], la), face(a0, aa[y - 1][z][k], la), uyp, u0, uym, p.ih2[1],
+                        p.cadv[1]);
           if constexpr (D == 3) {
             const double uzm = uu[y][z - 1][k], uzp = mz ? uzm : uu[y][z + 1][k];
-            v += ((0.5 * (a0 + aa[y][z + 1][k]) - la) * (uzp - u0) - (0.5 * (a0 + aa[y][z - 1][k]) - la) * (u0 - uzm)) *
-                     p.ih2[2] +
-                 p.cadv[2] * (uzp - uzm);
+            v = flux_axis(v, face(a0, aa[y][z + 1][k], la), face(a0, aa[y][z - 1][k], la), uzp, u0, uzm, p.ih2[2],
+                          p.cadv[2]);
           }
         }
-        v += p.r0 + u0 * (p.r1 + u0 * (p.r2 + u0 * p.r3));
+        v += reaction(p, u0);
         g[k] = v;
       }
       if (p.sub) {
@@ -358,10 +370,10 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
         for (int k = 0; k < P; ++k) o[k] = p.c0 * g[k];
       } else if (p.base0 == u) {
 #pragma unroll
-        for (int k = 0; k < P; ++k) o[k] = uc[k] + p.c0 * g[k];
+        for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c0, g[k], uc[k]);
       } else {
 #pragma unroll
-        for (int k = 0; k < P; ++k) o[k] = wb[y - 1][z - ZB][k] + p.c0 * g[k];
+        for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c0, g[k], wb[y - 1][z - ZB][k]);
       }
       if (p.flag) {
         bool bad = false;
@@ -376,7 +388,7 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
         write_row_digits<P, S>(o, ucnt, x, row, p, kp);
         if (p.drow1) {   // base1 is u or null (checked at launch)
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] = (p.base1 ? uc[k] : 0.0) + p.c1 * g[k];
+          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], p.base1 ? uc[k] : 0.0);
           write_row_digits<P, S>(o, ucnt, x, p.drow1 + row, p, kp);
         }
         continue;
@@ -391,11 +403,11 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
           for (int k = 0; k < P; ++k) o[k] = p.c1 * g[k];
         } else if (p.base1 == u) {
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] = uc[k] + p.c1 * g[k];
+          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], uc[k]);
         } else {
           load_row<P>(o, p.base1, idx, nu, ucnt);
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] += p.c1 * g[k];
+          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], o[k]);
         }
         if (p.out1f)
           store_row<P>(p.out1f, idxo, o, ucnt);
@@ -496,6 +508,261 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
     launch_batch_d<3>(P, b, count, sg, (unsigned)blocks, s);
   else
     launch_batch_d<2>(P, b, count, sg, (unsigned)blocks, s);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- two stages at once
+// Between two Lawson2b steps in 3D, the last stage of one and the first of the next:
+//   u+ = W + c0 g(U),  out0 = u+ + c1 g(u+),  out1 = u+ + c0 g(u+),
+// without u+ ever going to memory: five passes over grid functions instead of eight, and each x3
+// plane read about once. A block takes W = 512 NQ - 2 n1 consecutive points of the (x1, x2) plane
+// in row-major order (whatever the row length) and walks along x3 over zc planes. A thread owns NQ
+// points, 512 apart, of the run widened by one row on either side, where it computes u+; the
+// neighbours along x1 and x2 of U and a are read from LDS (two planes of each, loaded one
+// plane ahead), those of u+ likewise from LDS one plane later, and what lies along x3
+// (U, u+, faces) stays in the thread's registers.
+// Every access to memory is a buffer access with the plane's size, at an offset past it where a
+// lane has nothing to load or store: no branch splits the loads in flight.
+constexpr int TP = 512;
+__host__ __device__ constexpr int pair_loads(int nq) { return nq + 2; }   // of a thread per run
+constexpr unsigned kNone = 0x80000000u;
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_of(const double* base, int64_t at, int64_t len, bool any) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base + (any ? at : 0)), 0, any ? (int)(8 * len) : 0,
+                                           0x00020000);
+}
+__device__ __forceinline__ double plane_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+__device__ __forceinline__ void plane_store(__amdgpu_buffer_rsrc_t r, unsigned off, double v) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, v), r, off, 0, 2 /* nontemporal */);
+}
+// bound on the elements of the run that holds w consecutive points of rows of n1 (pitch p) and
+// their neighbours along x1 and x2
+__host__ __device__ inline int run_elems(int w, int n1, int p) {
+  return ((w - 1) / n1 + 1) * (p - n1) + w + 2 * p + 4;
+}
+
+template <int NQ>
+__global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(StencilBatch batch, int nruns, int zc) {
+  constexpr int NL = pair_loads(NQ);
+  const StencilArgs& p = batch.a[blockIdx.y];
+  extern __shared__ __attribute__((aligned(16))) double pair_lds[];
+  const int n1 = p.n1, n2 = p.n2, n3 = p.n3, tid = threadIdx.x;
+  const int pu = p.ldi ? p.ldi : n1, pa = n1 + 2;
+  const int64_t su = (int64_t)pu * n2, sa = (int64_t)pa * (n2 + 2);   // planes
+  const int plane = n1 * n2, W = TP * NQ - 2 * n1;
+  const int e0 = (int)(blockIdx.x % nruns) * W, zs = (int)(blockIdx.x / nruns) * zc, ze = min(zs + zc, n3);
+  const int lo = e0 - n1, hi = lo + TP * NQ - 1;   // own points (some outside the plane)
+  const int Lu = run_elems(TP * NQ, n1, pu), La = run_elems(TP * NQ, n1, pa);
+  double* const Us = pair_lds;          // [2][Lu]: U in planes z, z + 1; zero outside the grid
+  double* const As = Us + 2 * Lu;       // [2][La]: a likewise
+  double* const Ps = As + 2 * La;       // [TP NQ + 2]: u+ of the own points in plane z - 1 (n1 more are read)
+  // the first element of a run in a plane of U (negative: in the row before the first) and of a,
+  // and the part of it inside the plane
+  const int rlo = lo < 0 ? -1 : lo / n1, clo = lo - rlo * n1;
+  const int bu = rlo * pu + clo - pu - 1;
+  const int rhi = hi / n1, chi = hi - rhi * n1;
+  const int u0 = max(bu, 0), lu = min(rhi * pu + chi + pu + 2, (int)su) - u0;
+  const int l0 = max(lo, 0), l1 = min(hi, plane - 1);
+  const int ba = (l0 / n1) * pa + l0 % n1, la = (l1 / n1 + 2) * pa + l1 % n1 + 3 - ba;
+  for (int e = tid; e < 2 * Lu + 2 * La + TP * NQ + 2 + n1; e += TP) pair_lds[e] = 0.0;
+
+  double ru[NL], ra[NL], rw[NQ];
+  // (a plane outside the grid, or not wanted: zeros)
+  auto load_u = [&](int z, bool any) {
+    const __amdgpu_buffer_rsrc_t r = plane_of(p.u, z * su, su, any && z >= 0 && z < n3);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int k = tid + TP * i;
+      ru[i] = plane_load(r, k < lu ? 8u * (unsigned)(u0 + k) : kNone);
+    }
+  };
+  auto load_a = [&](int z, bool any) {   // -1 <= z <= n3
+    const __amdgpu_buffer_rsrc_t r = plane_of(p.a, (z + 1) * sa, sa, any);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int k = tid + TP * i;
+      ra[i] = plane_load(r, k < la ? 8u * (unsigned)(ba + k) : kNone);
+    }
+  };
+  auto put = [&](double* dst, const double (&r)[NL], int len) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      if (tid + TP * i < len) dst[tid + TP * i] = r[i];
+  };
+  auto put_u = [&](int z) { put(Us + (z & 1) * Lu + u0 - bu, ru, lu); };
+  auto put_a = [&](int z) { put(As + (z & 1) * La, ra, la); };
+
+  int iu[NQ], ia[NQ];                    // positions in a plane of U, of a
+  bool in[NQ], own[NQ], x0[NQ], x1[NQ];   // inside the plane; of this block's run; ends of x1
+  // U at z - 1; faces along x3 at z - 1/2 and z - 3/2; u+ at z - 1 and z - 2; faces of plane z - 1
+  double Um[NQ], czm[NQ], czmm[NQ], pm[NQ], pmm[NQ], cxp[NQ], cxm[NQ], cyp[NQ], cym[NQ];
+  const double lam = p.lam_amax;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int e = lo + tid + TP * q;
+    in[q] = e >= 0 && e < plane;
+    own[q] = in[q] && e >= e0 && e < e0 + W;
+    const int ec = in[q] ? e : e0, i2 = ec / n1, i1 = ec - i2 * n1;
+    iu[q] = i2 * pu + i1;
+    ia[q] = (i2 + 1) * pa + i1 + 1;
+    x0[q] = i1 == 0;
+    x1[q] = i1 == n1 - 1;
+    Um[q] = zs >= 2 ? p.u[(zs - 2) * su + iu[q]] : 0.0;
+    czm[q] = zs >= 1 ? face(p.a[zs * sa + ia[q]], p.a[(zs - 1) * sa + ia[q]], lam) : 0.0;
+    czmm[q] = pm[q] = pmm[q] = cxp[q] = cxm[q] = cyp[q] = cym[q] = 0.0;
+    rw[q] = zs >= 1 ? p.base0[(zs - 1) * su + iu[q]] : 0.0;
+  }
+  __syncthreads();   // (the LDS is cleared)
+  load_u(zs - 1, true);
+  load_a(zs - 1, true);
+  put_u(zs - 1);
+  put_a(zs - 1);
+  load_u(zs, true);
+  load_a(zs, true);
+  put_u(zs);
+  put_a(zs);
+  __syncthreads();
+
+  bool bad = false;
+  for (int z = zs - 1; z <= ze; ++z) {
+    const double* const U0 = Us + (z & 1) * Lu - bu;
+    const double* const U1 = Us + ((z + 1) & 1) * Lu - bu;
+    const double* const A0 = As + (z & 1) * La - ba;
+    const double* const A1 = As + ((z + 1) & 1) * La - ba;
+    double w[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) w[q] = rw[q];
+    const bool more = z < ze;
+    load_u(z + 2, more);
+    load_a(min(z + 2, n3), more);
+    {
+      const __amdgpu_buffer_rsrc_t r = plane_of(p.base0, (z + 1) * su, su, more && z + 1 < n3);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) rw[q] = plane_load(r, 8u * (unsigned)iu[q]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const bool grid = z >= 0 && z < n3, out = z > zs, mine = z >= zs && z < ze;
+    const __amdgpu_buffer_rsrc_t o0 = plane_of(p.out0, (z - 1) * su, su, out), o1 = plane_of(p.out1, (z - 1) * su, su, out);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const double *a = A0 + ia[q], *u = U0 + iu[q];
+      const double a0 = a[0], czp = face(a0, A1[ia[q]], lam);
+      const double nxp = face(a0, a[1], lam), nxm = face(a0, a[-1], lam);
+      const double nyp = face(a0, a[pa], lam), nym = face(a0, a[-pa], lam);
+      const double uc = u[0], uzp = U1[iu[q]], lxm = u[-1], lxp = u[1], uym = u[-pu], uyp = u[pu];
+      const double uxm = x0[q] ? 0.0 : lxm, uxp = x1[q] ? 0.0 : lxp;
+      double g = flux_axis(0.0, nxp, nxm, uxp, uc, uxm, p.ih2[0], p.cadv[0]);
+      g = flux_axis(g, nyp, nym, uyp, uc, uym, p.ih2[1], p.cadv[1]);
+      g = flux_axis(g, czp, czm[q], uzp, uc, Um[q], p.ih2[2], p.cadv[2]);
+      g += reaction(p, uc);
+      double up = __builtin_fma(p.c0, g, w[q]);
+      up = in[q] && grid ? up : 0.0;
+      bad |= own[q] && mine && !(fabs(up) <= DBL_MAX);
+      // the stages of plane z - 1 (other threads' points and planes: not stored)
+      const double* P = Ps + 1 + tid + TP * q;
+      const double lm = P[-1], lp = P[1], pym = P[-n1], pyp = P[n1], pc = pm[q];
+      const double pxm = x0[q] ? 0.0 : lm, pxp = x1[q] ? 0.0 : lp;
+      g = flux_axis(0.0, cxp[q], cxm[q], pxp, pc, pxm, p.ih2[0], p.cadv[0]);
+      g = flux_axis(g, cyp[q], cym[q], pyp, pc, pym, p.ih2[1], p.cadv[1]);
+      g = flux_axis(g, czm[q], czmm[q], up, pc, pmm[q], p.ih2[2], p.cadv[2]);
+      g += reaction(p, pc);
+      const unsigned o = own[q] ? 8u * (unsigned)iu[q] : kNone;
+      plane_store(o0, o, __builtin_fma(p.c1, g, pc));
+      plane_store(o1, o, __builtin_fma(p.c0, g, pc));
+      pmm[q] = pm[q];
+      pm[q] = up;
+      czmm[q] = czm[q];
+      czm[q] = czp;
+      cxp[q] = nxp;
+      cxm[q] = nxm;
+      cyp[q] = nyp;
+      cym[q] = nym;
+      Um[q] = uc;
+    }
+    if (!more) break;
+    __syncthreads();   // plane z of U and a and u+ of plane z - 1 have been read
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) Ps[1 + tid + TP * q] = pm[q];
+    put_u(z + 2);
+    put_a(z + 2);
+    __syncthreads();
+  }
+  if (bad && p.flag) p.flag[0] = 1;
+}
+
+// The split of `count` grids: the NQ and the planes per block of the least estimated time, in
+// units of one point of every thread in one plane (a block's two extra planes and its start, about
+// two more; whole rounds of the blocks that the LDS lets run together). 0: not for this kernel.
+static double pair_split(const StencilArgs& a, int count, int& NQ, int& zc, size_t& lds) {
+  if (a.n1 < 2 || a.n3 < 2 || (int64_t)a.n1 * a.n2 > (1 << 24)) return 0.0;
+  const int pu = a.ldi ? a.ldi : a.n1;
+  double best = 0.0;
+  for (int q = 1; q <= 5; ++q) {
+    const int R = TP * q, W = R - 2 * a.n1, Lu = run_elems(R, a.n1, pu), La = run_elems(R, a.n1, a.n1 + 2);
+    const size_t bytes = sizeof(double) * (2 * (size_t)Lu + 2 * La + R + 2 + a.n1);
+    if (W < a.n1 || std::max(Lu, La) > TP * pair_loads(q) || bytes > 160 * 1024) continue;
+    const int occ = std::min<int>(160 * 1024 / bytes, q <= 2 ? 2 : 1);
+    const int64_t runs = ((int64_t)a.n1 * a.n2 + W - 1) / W;
+    for (int z = 2; z <= a.n3 && z <= 64; ++z) {
+      const int64_t blocks = runs * ((a.n3 + z - 1) / z) * count;
+      const double rounds = (double)((blocks + 256 * occ - 1) / (256 * occ));
+      const double cost = rounds * occ * q * (z + 4);
+      if (best == 0.0 || cost < best) {
+        best = cost;
+        NQ = q;
+        zc = z;
+        lds = bytes;
+      }
+    }
+  }
+  return best;
+}
+
+static bool pair_accepts(const StencilArgs& a) {
+  return !a.nondiv && !a.sub && !a.dig && !a.out0f && !a.out1f && !a.neu[0] && !a.neu[1] && !a.neu[2] && a.ldi == a.ldo;
+}
+
+// Where the one launch is the faster: its estimate (0.7 us a unit: 8.5 k clocks measured for five)
+// against that of two launches of stencil_batch_kernel (7 ns per 1000 lanes, idle ones included),
+// 3 us for each launch, and a margin for the estimates. Measured per step, two launches -> one: 63^3
+// 28.7 -> 31.3 us (stays), 96^3 56 -> 57 (stays), 110^3 81 -> 77.6, 127^3 95 -> 93, 130 x 129 x 127
+// 126 -> 112, 160^3 191 -> 172, 210^3 430 -> 378, 255^3 685 -> 635, 30 x 200 x 150 76 -> 64.5,
+// 200 x 30 x 150 67 -> 69 (stays).
+bool stencil_pair_pays(int d, const StencilArgs& a, int count) {
+  if (d != 3 || !pair_accepts(a)) return false;
+  int NQ, zc, P;
+  size_t lds;
+  StencilGrid sg;
+  int64_t blocks;
+  const double cost = pair_split(a, count, NQ, zc, lds);
+  if (cost == 0.0 || !stencil_grid(d, a.n1, a.n2, a.n3, false, P, sg, blocks)) return false;
+  const double lanes = (double)blocks * (64 * SW) * P * 2 * count;
+  return 1.1 * (3.0 + 0.7 * cost) < 2.0 * (3.0 + 7e-6 * lanes);
+}
+
+hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s) {
+  if (count < 1 || count > kMaxGroups) return hipErrorInvalidValue;
+  StencilBatch b;
+  for (int i = 0; i < count; ++i) {
+    if (!pair_accepts(a[i]) || a[i].n1 != a[0].n1 || a[i].n2 != a[0].n2 || a[i].n3 != a[0].n3 ||
+        a[i].ldi != a[0].ldi || !a[i].u || !a[i].a || !a[i].base0 || !a[i].out0 || !a[i].out1)
+      return hipErrorInvalidValue;
+    b.a[i] = a[i];
+  }
+  int NQ, zc;
+  size_t lds;
+  if (pair_split(a[0], count, NQ, zc, lds) == 0.0) return hipErrorInvalidValue;
+  const int W = TP * NQ - 2 * a[0].n1, nruns = (a[0].n1 * a[0].n2 + W - 1) / W;
+  const dim3 grid((unsigned)nruns * (unsigned)((a[0].n3 + zc - 1) / zc), (unsigned)count);
+  switch (NQ) {
+    case 1: stencil_pair_kernel<1><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+    case 2: stencil_pair_kernel<2><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+    case 3: stencil_pair_kernel<3><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+    case 4: stencil_pair_kernel<4><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+    default: stencil_pair_kernel<5><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+  }
   return hipGetLastError();
 }
 
