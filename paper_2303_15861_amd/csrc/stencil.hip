@@ -552,7 +552,11 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
   const int pu = p.ldi ? p.ldi : n1, pa = n1 + 2;
   const int64_t su = (int64_t)pu * n2, sa = (int64_t)pa * (n2 + 2);   // planes
   const int plane = n1 * n2, W = TP * NQ - 2 * n1;
-  const int e0 = (int)(blockIdx.x % nruns) * W, zs = (int)(blockIdx.x / nruns) * zc, ze = min(zs + zc, n3);
+  // consecutive runs of a chunk of planes on one XCD (blocks go to the XCDs in turn), so that the
+  // rows that two of them read come from its L2 the second time
+  const int B = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int e0 = B % nruns * W, zs = B / nruns * zc, ze = min(zs + zc, n3);
+  if (zs >= n3) return;   // (the grid is rounded up to whole eights)
   const int lo = e0 - n1, hi = lo + TP * NQ - 1;   // own points (some outside the plane)
   const int Lu = run_elems(TP * NQ, n1, pu), La = run_elems(TP * NQ, n1, pa);
   double* const Us = pair_lds;          // [2][Lu]: U in planes z, z + 1; zero outside the grid
@@ -566,11 +570,9 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
   const int u0 = max(bu, 0), lu = min(rhi * pu + chi + pu + 2, (int)su) - u0;
   const int l0 = max(lo, 0), l1 = min(hi, plane - 1);
   const int ba = (l0 / n1) * pa + l0 % n1, la = (l1 / n1 + 2) * pa + l1 % n1 + 3 - ba;
-  for (int e = tid; e < 2 * Lu + 2 * La + TP * NQ + 2 + n1; e += TP) pair_lds[e] = 0.0;
 
-  double ru[NL], ra[NL], rw[NQ];
   // (a plane outside the grid, or not wanted: zeros)
-  auto load_u = [&](int z, bool any) {
+  auto load_u = [&](double (&ru)[NL], int z, bool any) {
     const __amdgpu_buffer_rsrc_t r = plane_of(p.u, z * su, su, any && z >= 0 && z < n3);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
       ru[i] = plane_load(r, k < lu ? 8u * (unsigned)(u0 + k) : kNone);
     }
   };
-  auto load_a = [&](int z, bool any) {   // -1 <= z <= n3
+  auto load_a = [&](double (&ra)[NL], int z, bool any) {   // -1 <= z <= n3
     const __amdgpu_buffer_rsrc_t r = plane_of(p.a, (z + 1) * sa, sa, any);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -591,8 +593,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     for (int i = 0; i < NL; ++i)
       if (tid + TP * i < len) dst[tid + TP * i] = r[i];
   };
-  auto put_u = [&](int z) { put(Us + (z & 1) * Lu + u0 - bu, ru, lu); };
-  auto put_a = [&](int z) { put(As + (z & 1) * La, ra, la); };
+  auto put_u = [&](const double (&ru)[NL], int z) { put(Us + (z & 1) * Lu + u0 - bu, ru, lu); };
+  auto put_a = [&](const double (&ra)[NL], int z) { put(As + (z & 1) * La, ra, la); };
 
   int iu[NQ], ia[NQ];                    // positions in a plane of U, of a
   bool in[NQ], own[NQ], x0[NQ], x1[NQ];   // inside the plane; of this block's run; ends of x1
@@ -609,20 +611,35 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     ia[q] = (i2 + 1) * pa + i1 + 1;
     x0[q] = i1 == 0;
     x1[q] = i1 == n1 - 1;
-    Um[q] = zs >= 2 ? p.u[(zs - 2) * su + iu[q]] : 0.0;
-    czm[q] = zs >= 1 ? face(p.a[zs * sa + ia[q]], p.a[(zs - 1) * sa + ia[q]], lam) : 0.0;
     czmm[q] = pm[q] = pmm[q] = cxp[q] = cxm[q] = cyp[q] = cym[q] = 0.0;
-    rw[q] = zs >= 1 ? p.base0[(zs - 1) * su + iu[q]] : 0.0;
   }
-  __syncthreads();   // (the LDS is cleared)
-  load_u(zs - 1, true);
-  load_a(zs - 1, true);
-  put_u(zs - 1);
-  put_a(zs - 1);
-  load_u(zs, true);
-  load_a(zs, true);
-  put_u(zs);
-  put_a(zs);
+  // the first planes, all in flight at once
+  double ru[NL], ra[NL], rw[NQ];
+  {
+    double su1[NL], sa1[NL], am[NQ], a0[NQ];
+    load_u(ru, zs - 1, true);
+    load_a(ra, zs - 1, true);
+    load_u(su1, zs, true);
+    load_a(sa1, zs, true);
+    const __amdgpu_buffer_rsrc_t u2 = plane_of(p.u, (zs - 2) * su, su, zs >= 2), w1 = plane_of(p.base0, (zs - 1) * su, su, zs >= 1);
+    const __amdgpu_buffer_rsrc_t a2 = plane_of(p.a, (zs - 1) * sa, sa, zs >= 1), a1 = plane_of(p.a, zs * sa, sa, true);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      Um[q] = plane_load(u2, 8u * (unsigned)iu[q]);
+      rw[q] = plane_load(w1, 8u * (unsigned)iu[q]);
+      am[q] = plane_load(a2, 8u * (unsigned)ia[q]);
+      a0[q] = plane_load(a1, 8u * (unsigned)ia[q]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int e = tid; e < 2 * Lu + 2 * La + TP * NQ + 2 + n1; e += TP) pair_lds[e] = 0.0;
+    __syncthreads();
+    put_u(ru, zs - 1);
+    put_a(ra, zs - 1);
+    put_u(su1, zs);
+    put_a(sa1, zs);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) czm[q] = face(a0[q], am[q], lam);   // (zs = 0: not used)
+  }
   __syncthreads();
 
   bool bad = false;
@@ -635,8 +652,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
 #pragma unroll
     for (int q = 0; q < NQ; ++q) w[q] = rw[q];
     const bool more = z < ze;
-    load_u(z + 2, more);
-    load_a(min(z + 2, n3), more);
+    load_u(ru, z + 2, more);
+    load_a(ra, min(z + 2, n3), more);
     {
       const __amdgpu_buffer_rsrc_t r = plane_of(p.base0, (z + 1) * su, su, more && z + 1 < n3);
 #pragma unroll
@@ -685,8 +702,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     __syncthreads();   // plane z of U and a and u+ of plane z - 1 have been read
 #pragma unroll
     for (int q = 0; q < NQ; ++q) Ps[1 + tid + TP * q] = pm[q];
-    put_u(z + 2);
-    put_a(z + 2);
+    put_u(ru, z + 2);
+    put_a(ra, z + 2);
     __syncthreads();
   }
   if (bad && p.flag) p.flag[0] = 1;
@@ -755,7 +772,7 @@ hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s) {
   size_t lds;
   if (pair_split(a[0], count, NQ, zc, lds) == 0.0) return hipErrorInvalidValue;
   const int W = TP * NQ - 2 * a[0].n1, nruns = (a[0].n1 * a[0].n2 + W - 1) / W;
-  const dim3 grid((unsigned)nruns * (unsigned)((a[0].n3 + zc - 1) / zc), (unsigned)count);
+  const dim3 grid(((unsigned)nruns * (unsigned)((a[0].n3 + zc - 1) / zc) + 7) / 8 * 8, (unsigned)count);
   switch (NQ) {
     case 1: stencil_pair_kernel<1><<<grid, TP, lds, s>>>(b, nruns, zc); break;
     case 2: stencil_pair_kernel<2><<<grid, TP, lds, s>>>(b, nruns, zc); break;
