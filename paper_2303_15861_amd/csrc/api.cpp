@@ -1843,6 +1843,16 @@ mm_status mumode_expv(mm_ctx* ctx, const mm_op* op, int j, const double* in, dou
   // small grids keep the plain products, whose sums are those of mumode_expv_noalloc (it has
   // no folded factors): the two agree bit for bit on every grid that the latter takes
   const Layout dense{0, 0};
+  if (op->prec == MM_FP64 && !op->periodic && ctx->gemm_tile == 0 &&
+      slab_fits(op->d, op->n[0], op->n[1], op->n[2])) {
+    // (as mumode_expv_noalloc; a product tile set by the caller keeps the separate products)
+    HIPCHK(ctx, timed_launch(ctx, MM_KIND_FUSED, 2.0 * (double)op->dof * (op->n[0] + op->n[1]), s, [&] {
+      return launch_slab_action(in, factor(op, 0, j), factor(op, 1, j), t0, op->n[0], op->n[1], op->n[2], s);
+    }));
+    HIPCHK(ctx, pass_last(op, factor_op(op, 2, j), factor_exp(op, 2, j), 1, t0, out, nullptr, 1.0, 0.0, 1,
+                          PassIO{false, false, false, true}, s, dense, dense, folded(op, 2, j)));
+    return MM_OK;
+  }
   HIPCHK(ctx, exp_action(op, j, in, false, out, 1, t0, t1, s, nullptr, 1.0, 1.0, dense, dense, dense, false, true));
   return MM_OK;
 }

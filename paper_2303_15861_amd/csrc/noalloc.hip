@@ -122,10 +122,14 @@ extern "C" mm_status mumode_expv_noalloc(mm_ctx* ctx, int d, const int* n, const
   double* s1 = base + mm::kNoAllocMaxDof;
   int nn[3] = {n[0], n[1], d == 3 ? n[2] : 1};
   const int tile = ctx->gemm_tile;
-  hipError_t e;
+  hipError_t e = hipSuccess;
   // 3D: in -> s0 -> s1 -> out; 2D: in -> s0 -> out (in and out may alias)
-  e = mm::fp64_pass(d, nn, 0, E[0], in, s0, tile, s);
-  if (e == hipSuccess && d == 3) e = mm::fp64_pass(d, nn, 1, E[1], s0, s1, tile, s);
+  if (tile == 0 && mm::slab_fits(d, nn[0], nn[1], nn[2])) {
+    e = mm::launch_slab_action(in, E[0], E[1], s1, nn[0], nn[1], nn[2], s);
+  } else {
+    e = mm::fp64_pass(d, nn, 0, E[0], in, s0, tile, s);
+    if (e == hipSuccess && d == 3) e = mm::fp64_pass(d, nn, 1, E[1], s0, s1, tile, s);
+  }
   if (e == hipSuccess) e = mm::fp64_pass(d, nn, d - 1, E[d - 1], d == 3 ? s1 : s0, out, tile, s);
   if (e != hipSuccess) {
     ctx->last_error = std::string("mumode_expv_noalloc: launch failed: ") + hipGetErrorString(e);

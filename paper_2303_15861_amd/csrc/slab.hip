@@ -8,7 +8,8 @@
 // (the remainder reads the planes above and below straight from memory), multiplies it by
 // E1 along x1 and by E2 along x2 in LDS, and writes the result once; the product along x3
 // follows as a mode product of its own. 60^3: 12-13.5 us for one or two vectors, against
-// 5.2 us of stencil and 5-6 us per product and vector. 2 T waves, T = ceil(max(n1, n2)/16), each with the
+// 5.2 us of stencil and 5-6 us per product and vector. Without a remainder the slab is read, multiplied
+// twice and written (launch_slab_action). 2 T waves, T = ceil(max(n1, n2)/16), each with the
 // factor rows of one tile of either product in registers.
 #include <cfloat>
 
@@ -231,6 +232,20 @@ __global__ __launch_bounds__(128 * T, 2) void slab_products(SlabArgs p) {
 
 bool slab_fits(int d, int n1, int n2, int n3) {
   return d == 3 && n1 >= 2 && n2 >= 2 && n3 >= 1 && n1 <= kSlabMax && n2 <= kSlabMax && n3 <= 65535;
+}
+
+hipError_t launch_slab_action(const double* u, const double* E1, const double* E2, double* out, int n1, int n2, int n3,
+                              hipStream_t s) {
+  SlabArgs a{};
+  a.u = a.a = u;   // (without a remainder the coefficient is not read)
+  a.n1 = n1;
+  a.n2 = n2;
+  a.n3 = n3;
+  a.base[0] = 1;
+  a.E1[0] = E1;
+  a.E2[0] = E2;
+  a.out[0] = out;
+  return launch_slab(a, 1, s);
 }
 
 hipError_t launch_slab(const SlabArgs& a, int nvec, hipStream_t s) {
