@@ -1689,8 +1689,9 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
                                       unit ? 1.0 : op->weight[j], st));
     }
     // the stacked factors' blocks are weighted exp factors of the last axis: they fold
-    // where that axis's factors do
-    if (prec == MM_FP64 && op->ffold[la]) {
+    // where that axis's factors do (in the sine basis none is used: without it, at fold mode 0,
+    // nothing folds)
+    if (prec == MM_FP64 && op->ffold[la] && !op->sine) {
       const int64_t fb = (int64_t)2 * (nl - nl / 2) * fold_ld(nl);
       if ((rc = dev_alloc(op, &op->f3_stage1_fold, fb * g1)) != MM_OK) return fail(rc);
       if ((rc = dev_alloc(op, &op->f3_stage2_fold, fb * q)) != MM_OK) return fail(rc);

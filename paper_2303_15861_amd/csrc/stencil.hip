@@ -151,8 +151,8 @@ __device__ __forceinline__ void write_row_digits(const double (&v)[P], int cnt, 
 
 // The flux form's arithmetic, with its multiply-adds written out: stencil_body and
 // stencil_pair_kernel agree bit for bit.
-// less the extracted part, the mean of a at a face
-__device__ __forceinline__ double face(double a0, double a1, double la) { return __builtin_fma(0.5, a0 + a1, -la); }
+// half of a less the extracted part; a face coefficient (their mean) is the sum of its two nodes'
+__device__ __forceinline__ double half_node(double a, double la) { return __builtin_fma(0.5, a, -0.5 * la); }
 // v + one axis' part of g at a point (u0) between um and up, with the faces cm and cp
 __device__ __forceinline__ double flux_axis(double v, double cp, double cm, double up, double u0, double um, double ih2,
                                             double cadv) {
@@ -345,12 +345,14 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
           }
         } else {
           const double axm = (k == 0) ? al : ac[k - 1], axp = (k == P - 1) ? ar : ac[k + 1];
-          v = flux_axis(0.0, face(a0, axp, la), face(a0, axm, la), uxp, u0, uxm, p.ih2[0], p.cadv[0]);
-          v = flux_axis(v, face(a0, aa[y + 1][z][k], la), face(a0, aa[y - 1][z][k], la), uyp, u0, uym, p.ih2[1],
+          const double h0 = half_node(a0, la);
+          auto face = [&](double a) { return h0 + half_node(a, la); };
+          v = flux_axis(0.0, face(axp), face(axm), uxp, u0, uxm, p.ih2[0], p.cadv[0]);
+          v = flux_axis(v, face(aa[y + 1][z][k]), face(aa[y - 1][z][k]), uyp, u0, uym, p.ih2[1],
                         p.cadv[1]);
           if constexpr (D == 3) {
             const double uzm = uu[y][z - 1][k], uzp = mz ? uzm : uu[y][z + 1][k];
-            v = flux_axis(v, face(a0, aa[y][z + 1][k], la), face(a0, aa[y][z - 1][k], la), uzp, u0, uzm, p.ih2[2],
+            v = flux_axis(v, face(aa[y][z + 1][k]), face(aa[y][z - 1][k]), uzp, u0, uzm, p.ih2[2],
                           p.cadv[2]);
           }
         }
@@ -520,7 +522,10 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
 // points, 512 apart, of the run widened by one row on either side, where it computes u+; the
 // neighbours along x1 and x2 of U and a are read from LDS (two planes of each, loaded one
 // plane ahead), those of u+ likewise from LDS one plane later, and what lies along x3
-// (U, u+, faces) stays in the thread's registers.
+// (U, u+, faces) stays in the thread's registers. 255^3: 195 us against 2 x 119 for the two launches
+// (440 MB read, 290 MB written: not the traffic but about 120 vector instructions a point, 63 of
+// them arithmetic, and two barriers a plane bound it; loading two planes ahead gained nothing).
+// 127^3 32 against 2 x 17.5, 130 x 129 x 127 36 against 2 x 26.
 // Every access to memory is a buffer access with the plane's size, at an offset past it where a
 // lane has nothing to load or store: no branch splits the loads in flight.
 constexpr int TP = 512;
@@ -543,7 +548,8 @@ __host__ __device__ inline int run_elems(int w, int n1, int p) {
   return ((w - 1) / n1 + 1) * (p - n1) + w + 2 * p + 4;
 }
 
-template <int NQ>
+// PAD: the rows have padding, which is zero, so the x1 neighbours beyond their ends need no masks.
+template <int NQ, int PAD>
 __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(StencilBatch batch, int nruns, int zc) {
   constexpr int NL = pair_loads(NQ);
   const StencilArgs& p = batch.a[blockIdx.y];
@@ -560,8 +566,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
   const int lo = e0 - n1, hi = lo + TP * NQ - 1;   // own points (some outside the plane)
   const int Lu = run_elems(TP * NQ, n1, pu), La = run_elems(TP * NQ, n1, pa);
   double* const Us = pair_lds;          // [2][Lu]: U in planes z, z + 1; zero outside the grid
-  double* const As = Us + 2 * Lu;       // [2][La]: a likewise
-  double* const Ps = As + 2 * La;       // [TP NQ + 2]: u+ of the own points in plane z - 1 (n1 more are read)
+  double* const As = Us + 2 * Lu;       // [2][La]: a likewise, as half_node
+  double* const Ps = As + 2 * La;       // [Lu]: u+ of the own points in plane z - 1, laid out as U
   // the first element of a run in a plane of U (negative: in the row before the first) and of a,
   // and the part of it inside the plane
   const int rlo = lo < 0 ? -1 : lo / n1, clo = lo - rlo * n1;
@@ -571,6 +577,7 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
   const int l0 = max(lo, 0), l1 = min(hi, plane - 1);
   const int ba = (l0 / n1) * pa + l0 % n1, la = (l1 / n1 + 2) * pa + l1 % n1 + 3 - ba;
 
+  const double lam = p.lam_amax;
   // (a plane outside the grid, or not wanted: zeros)
   auto load_u = [&](double (&ru)[NL], int z, bool any) {
     const __amdgpu_buffer_rsrc_t r = plane_of(p.u, z * su, su, any && z >= 0 && z < n3);
@@ -594,13 +601,17 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
       if (tid + TP * i < len) dst[tid + TP * i] = r[i];
   };
   auto put_u = [&](const double (&ru)[NL], int z) { put(Us + (z & 1) * Lu + u0 - bu, ru, lu); };
-  auto put_a = [&](const double (&ra)[NL], int z) { put(As + (z & 1) * La, ra, la); };
+  auto put_a = [&](const double (&ra)[NL], int z) {
+    double h[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) h[i] = half_node(ra[i], lam);
+    put(As + (z & 1) * La, h, la);
+  };
 
-  int iu[NQ], ia[NQ];                    // positions in a plane of U, of a
+  int iu[NQ], ia[NQ];                    // positions in a plane of U (and Ps), of a
   bool in[NQ], own[NQ], x0[NQ], x1[NQ];   // inside the plane; of this block's run; ends of x1
   // U at z - 1; faces along x3 at z - 1/2 and z - 3/2; u+ at z - 1 and z - 2; faces of plane z - 1
   double Um[NQ], czm[NQ], czmm[NQ], pm[NQ], pmm[NQ], cxp[NQ], cxm[NQ], cyp[NQ], cym[NQ];
-  const double lam = p.lam_amax;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int e = lo + tid + TP * q;
@@ -631,14 +642,14 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
       a0[q] = plane_load(a1, 8u * (unsigned)ia[q]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    for (int e = tid; e < 2 * Lu + 2 * La + TP * NQ + 2 + n1; e += TP) pair_lds[e] = 0.0;
+    for (int e = tid; e < 3 * Lu + 2 * La; e += TP) pair_lds[e] = 0.0;
     __syncthreads();
     put_u(ru, zs - 1);
     put_a(ra, zs - 1);
     put_u(su1, zs);
     put_a(sa1, zs);
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) czm[q] = face(a0[q], am[q], lam);   // (zs = 0: not used)
+    for (int q = 0; q < NQ; ++q) czm[q] = half_node(a0[q], lam) + half_node(am[q], lam);   // (zs = 0: not used)
   }
   __syncthreads();
 
@@ -665,11 +676,10 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const double *a = A0 + ia[q], *u = U0 + iu[q];
-      const double a0 = a[0], czp = face(a0, A1[ia[q]], lam);
-      const double nxp = face(a0, a[1], lam), nxm = face(a0, a[-1], lam);
-      const double nyp = face(a0, a[pa], lam), nym = face(a0, a[-pa], lam);
+      const double a0 = a[0], czp = a0 + A1[ia[q]];
+      const double nxp = a0 + a[1], nxm = a0 + a[-1], nyp = a0 + a[pa], nym = a0 + a[-pa];
       const double uc = u[0], uzp = U1[iu[q]], lxm = u[-1], lxp = u[1], uym = u[-pu], uyp = u[pu];
-      const double uxm = x0[q] ? 0.0 : lxm, uxp = x1[q] ? 0.0 : lxp;
+      const double uxm = !PAD && x0[q] ? 0.0 : lxm, uxp = !PAD && x1[q] ? 0.0 : lxp;
       double g = flux_axis(0.0, nxp, nxm, uxp, uc, uxm, p.ih2[0], p.cadv[0]);
       g = flux_axis(g, nyp, nym, uyp, uc, uym, p.ih2[1], p.cadv[1]);
       g = flux_axis(g, czp, czm[q], uzp, uc, Um[q], p.ih2[2], p.cadv[2]);
@@ -678,9 +688,9 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
       up = in[q] && grid ? up : 0.0;
       bad |= own[q] && mine && !(fabs(up) <= DBL_MAX);
       // the stages of plane z - 1 (other threads' points and planes: not stored)
-      const double* P = Ps + 1 + tid + TP * q;
-      const double lm = P[-1], lp = P[1], pym = P[-n1], pyp = P[n1], pc = pm[q];
-      const double pxm = x0[q] ? 0.0 : lm, pxp = x1[q] ? 0.0 : lp;
+      const double* P = Ps - bu + iu[q];
+      const double lm = P[-1], lp = P[1], pym = P[-pu], pyp = P[pu], pc = pm[q];
+      const double pxm = !PAD && x0[q] ? 0.0 : lm, pxp = !PAD && x1[q] ? 0.0 : lp;
       g = flux_axis(0.0, cxp[q], cxm[q], pxp, pc, pxm, p.ih2[0], p.cadv[0]);
       g = flux_axis(g, cyp[q], cym[q], pyp, pc, pym, p.ih2[1], p.cadv[1]);
       g = flux_axis(g, czm[q], czmm[q], up, pc, pmm[q], p.ih2[2], p.cadv[2]);
@@ -701,7 +711,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     if (!more) break;
     __syncthreads();   // plane z of U and a and u+ of plane z - 1 have been read
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) Ps[1 + tid + TP * q] = pm[q];
+    for (int q = 0; q < NQ; ++q)
+      if (in[q]) Ps[iu[q] - bu] = pm[q];   // (zero outside the plane)
     put_u(ru, z + 2);
     put_a(ra, z + 2);
     __syncthreads();
@@ -718,7 +729,7 @@ static double pair_split(const StencilArgs& a, int count, int& NQ, int& zc, size
   double best = 0.0;
   for (int q = 1; q <= 5; ++q) {
     const int R = TP * q, W = R - 2 * a.n1, Lu = run_elems(R, a.n1, pu), La = run_elems(R, a.n1, a.n1 + 2);
-    const size_t bytes = sizeof(double) * (2 * (size_t)Lu + 2 * La + R + 2 + a.n1);
+    const size_t bytes = sizeof(double) * (3 * (size_t)Lu + 2 * La);
     if (W < a.n1 || std::max(Lu, La) > TP * pair_loads(q) || bytes > 160 * 1024) continue;
     const int occ = std::min<int>(160 * 1024 / bytes, q <= 2 ? 2 : 1);
     const int64_t runs = ((int64_t)a.n1 * a.n2 + W - 1) / W;
@@ -741,11 +752,11 @@ static bool pair_accepts(const StencilArgs& a) {
   return !a.nondiv && !a.sub && !a.dig && !a.out0f && !a.out1f && !a.neu[0] && !a.neu[1] && !a.neu[2] && a.ldi == a.ldo;
 }
 
-// Where the one launch is the faster: its estimate (0.7 us a unit: 8.5 k clocks measured for five)
+// Where the one launch is the faster: its estimate (0.7 us a unit: 3.5 us a plane measured for five)
 // against that of two launches of stencil_batch_kernel (7 ns per 1000 lanes, idle ones included),
 // 3 us for each launch, and a margin for the estimates. Measured per step, two launches -> one: 63^3
-// 28.7 -> 31.3 us (stays), 96^3 56 -> 57 (stays), 110^3 81 -> 77.6, 127^3 95 -> 93, 130 x 129 x 127
-// 126 -> 112, 160^3 191 -> 172, 210^3 430 -> 378, 255^3 685 -> 635, 30 x 200 x 150 76 -> 64.5,
+// 28.7 -> 31.3 us (stays), 96^3 56 -> 57 (stays), 110^3 81 -> 76, 127^3 95 -> 91, 130 x 129 x 127
+// 126 -> 108, 160^3 191 -> 171, 210^3 430 -> 375, 255^3 685 -> 627, 30 x 200 x 150 76 -> 64,
 // 200 x 30 x 150 67 -> 69 (stays).
 bool stencil_pair_pays(int d, const StencilArgs& a, int count) {
   if (d != 3 || !pair_accepts(a)) return false;
@@ -773,12 +784,14 @@ hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s) {
   if (pair_split(a[0], count, NQ, zc, lds) == 0.0) return hipErrorInvalidValue;
   const int W = TP * NQ - 2 * a[0].n1, nruns = (a[0].n1 * a[0].n2 + W - 1) / W;
   const dim3 grid(((unsigned)nruns * (unsigned)((a[0].n3 + zc - 1) / zc) + 7) / 8 * 8, (unsigned)count);
+  auto go = [&](auto kernel) { kernel<<<grid, TP, lds, s>>>(b, nruns, zc); };
+  const bool pad = a[0].ldi > a[0].n1;
   switch (NQ) {
-    case 1: stencil_pair_kernel<1><<<grid, TP, lds, s>>>(b, nruns, zc); break;
-    case 2: stencil_pair_kernel<2><<<grid, TP, lds, s>>>(b, nruns, zc); break;
-    case 3: stencil_pair_kernel<3><<<grid, TP, lds, s>>>(b, nruns, zc); break;
-    case 4: stencil_pair_kernel<4><<<grid, TP, lds, s>>>(b, nruns, zc); break;
-    default: stencil_pair_kernel<5><<<grid, TP, lds, s>>>(b, nruns, zc); break;
+    case 1: pad ? go(stencil_pair_kernel<1, 1>) : go(stencil_pair_kernel<1, 0>); break;
+    case 2: pad ? go(stencil_pair_kernel<2, 1>) : go(stencil_pair_kernel<2, 0>); break;
+    case 3: pad ? go(stencil_pair_kernel<3, 1>) : go(stencil_pair_kernel<3, 0>); break;
+    case 4: pad ? go(stencil_pair_kernel<4, 1>) : go(stencil_pair_kernel<4, 0>); break;
+    default: pad ? go(stencil_pair_kernel<5, 1>) : go(stencil_pair_kernel<5, 0>); break;
   }
   return hipGetLastError();
 }
