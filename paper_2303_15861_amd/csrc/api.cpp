@@ -2207,6 +2207,13 @@ double small_work(const mm_op* op, const SmallArgs& a) {
          (op->n[0] + op->n[1]);
 }
 
+// Whether the stages of op may run in pairs (launch_stencil_pair); their separate launches then
+// use the same arithmetic.
+int pair_form(const mm_op* op) {
+  return op->d == 3 && !op->periodic && op->scheme == MM_LAWSON2B && op->prec == MM_FP64 && op->form == MM_FORM_FLUX &&
+         op->bc[0] == MM_BC_DIRICHLET && op->bc[1] == MM_BC_DIRICHLET && op->bc[2] == MM_BC_DIRICHLET;
+}
+
 // The end of a Lawson2b step on the transformed pair [U, W] = res and the start of the next into
 // v (both padded): u+ = W + tau/2 g(U), v1 = u+ + tau g(u+), v2 = u+ + tau/2 g(u+).
 StencilArgs lawson2b_pair(const mm_op* op, const double* res, double* v) {
@@ -2221,7 +2228,7 @@ StencilArgs lawson2b_pair(const mm_op* op, const double* res, double* v) {
 }
 // whether the two run as one launch (bit for bit the two launches), for count such problems
 bool lawson2b_pairs(const mm_op* op, const double* res, double* v, int count) {
-  return op->scheme == MM_LAWSON2B && op->prec == MM_FP64 && res != v &&
+  return pair_form(op) && res != v &&
          stencil_pair_pays(op->d, lawson2b_pair(op, res, v), count);
 }
 
@@ -2318,6 +2325,7 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
         a.base1 = u;
         a.c1 = 0.5 * tau;
         a.ldo = op->ld1;
+        a.pair = pair_form(op);
         if (dg) {
           set_stencil_digits(a, op, op->vdig, op->vexp, 2);
           a.dchain = chain_active(op);
@@ -2346,6 +2354,7 @@ mm_status enqueue_lawson(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hi
       c.c0 = 0.5 * tau;
       c.ldi = op->ld1;
       c.out0 = u;
+      c.pair = pair_form(op);
       HIPCHK(ctx, stencil(op, c, s));
     }
   }
@@ -2771,6 +2780,7 @@ mm_status enqueue_lawson_group(mm_ctx* ctx, const mm_op* const* ops, double* con
         if (l2b) {
           a.base1 = u[i];
           a.c1 = 0.5 * op->tau;
+          a.pair = pair_form(op);
         }
         if (dg) {
           set_stencil_digits(a, op, ws->vdig + (int64_t)i * o0->slices * fib1 * slice_ld(o0->n[0]), ws->vexp + i * fib1,
@@ -2815,6 +2825,7 @@ mm_status enqueue_lawson_group(mm_ctx* ctx, const mm_op* const* ops, double* con
       c.c0 = 0.5 * op->tau;
       c.ldi = op->ld1;
       c.out0 = u[i];
+      c.pair = pair_form(op);
       sa[i] = c;
     }
     HIPCHK(ctx, timed_launch(ctx, MM_KIND_STENCIL, (double)dof * count, s,

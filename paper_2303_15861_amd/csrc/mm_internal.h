@@ -101,6 +101,7 @@ struct StencilArgs {
   int nondiv;           // diffusion a Lap u instead of div(a grad u)
   int full;             // F(u) requested instead of g(u) (periodic problems read this;
                         // the stencil gets F through lam_amax = 0 and cadv)
+  int pair;             // the arithmetic of launch_stencil_pair (3D stages of such steps)
   int ldi, ldo;         // x1 row strides of u/sub/base* and of out* (0: n1, unpadded)
   // MM_SLICED, rows of n1 <= 64 P values (one wave per row): out0 (and out1) are written
   // not in FP64 but as the grid operand of the mode-1 product, split into dS digit

@@ -149,8 +149,10 @@ __device__ __forceinline__ void write_row_digits(const double (&v)[P], int cnt, 
   }
 }
 
-// The flux form's arithmetic, with its multiply-adds written out: stencil_body and
-// stencil_pair_kernel agree bit for bit.
+// The flux form's arithmetic with its multiply-adds written out (PAIR), so that stencil_body and
+// stencil_pair_kernel agree bit for bit. Everything else keeps the expression as the compiler
+// contracts it: the low-precision modes turn a last-bit change of a stage into one of the size of
+// their own error.
 // half of a less the extracted part; a face coefficient (their mean) is the sum of its two nodes'
 __device__ __forceinline__ double half_node(double a, double la) { return __builtin_fma(0.5, a, -0.5 * la); }
 // v + one axis' part of g at a point (u0) between um and up, with the faces cm and cp
@@ -163,7 +165,7 @@ __device__ __forceinline__ double reaction(const StencilArgs& p, double u0) {
   return __builtin_fma(u0, __builtin_fma(u0, __builtin_fma(u0, p.r3, p.r2), p.r1), p.r0);
 }
 
-template <int D, int P, int S>
+template <int D, int P, int S, int PAIR>
 __device__ __forceinline__ void stencil_body(const StencilArgs& p, const StencilGrid& sg) {
   constexpr int YT = (D == 3) ? 1 : 2;   // rows per lane along x2
   constexpr int ZT = (D == 3 && S == 0) ? 2 : 1;   // rows per lane along x3
@@ -345,18 +347,28 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
           }
         } else {
           const double axm = (k == 0) ? al : ac[k - 1], axp = (k == P - 1) ? ar : ac[k + 1];
-          const double h0 = half_node(a0, la);
-          auto face = [&](double a) { return h0 + half_node(a, la); };
-          v = flux_axis(0.0, face(axp), face(axm), uxp, u0, uxm, p.ih2[0], p.cadv[0]);
-          v = flux_axis(v, face(aa[y + 1][z][k]), face(aa[y - 1][z][k]), uyp, u0, uym, p.ih2[1],
-                        p.cadv[1]);
+          if constexpr (PAIR) {
+            const double uzm = uu[y][z - 1][k], uzp = uu[y][z + 1][k], h0 = half_node(a0, la);
+            auto face = [&](double a) { return h0 + half_node(a, la); };
+            v = flux_axis(0.0, face(axp), face(axm), uxp, u0, uxm, p.ih2[0], p.cadv[0]);
+            v = flux_axis(v, face(aa[y + 1][z][k]), face(aa[y - 1][z][k]), uyp, u0, uym, p.ih2[1], p.cadv[1]);
+            v = flux_axis(v, face(aa[y][z + 1][k]), face(aa[y][z - 1][k]), uzp, u0, uzm, p.ih2[2], p.cadv[2]);
+            g[k] = v + reaction(p, u0);
+            continue;
+          }
+          v = ((0.5 * (a0 + axp) - la) * (uxp - u0) - (0.5 * (a0 + axm) - la) * (u0 - uxm)) * p.ih2[0] +
+              p.cadv[0] * (uxp - uxm);
+          v += ((0.5 * (a0 + aa[y + 1][z][k]) - la) * (uyp - u0) - (0.5 * (a0 + aa[y - 1][z][k]) - la) * (u0 - uym)) *
+                   p.ih2[1] +
+               p.cadv[1] * (uyp - uym);
           if constexpr (D == 3) {
             const double uzm = uu[y][z - 1][k], uzp = mz ? uzm : uu[y][z + 1][k];
-            v = flux_axis(v, face(aa[y][z + 1][k]), face(aa[y][z - 1][k]), uzp, u0, uzm, p.ih2[2],
-                          p.cadv[2]);
+            v += ((0.5 * (a0 + aa[y][z + 1][k]) - la) * (uzp - u0) - (0.5 * (a0 + aa[y][z - 1][k]) - la) * (u0 - uzm)) *
+                     p.ih2[2] +
+                 p.cadv[2] * (uzp - uzm);
           }
         }
-        v += reaction(p, u0);
+        v += p.r0 + u0 * (p.r1 + u0 * (p.r2 + u0 * p.r3));
         g[k] = v;
       }
       if (p.sub) {
@@ -366,16 +378,19 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
         for (int k = 0; k < P; ++k) g[k] -= sv[k];
       }
       // out0 = base0 + c0 g (base0 == u: from registers)
+      auto update = [](double base, double c, double s) {
+        return PAIR ? __builtin_fma(c, s, base) : base + c * s;
+      };
       double o[P];
       if (p.base0 == nullptr) {
 #pragma unroll
         for (int k = 0; k < P; ++k) o[k] = p.c0 * g[k];
       } else if (p.base0 == u) {
 #pragma unroll
-        for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c0, g[k], uc[k]);
+        for (int k = 0; k < P; ++k) o[k] = update(uc[k], p.c0, g[k]);
       } else {
 #pragma unroll
-        for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c0, g[k], wb[y - 1][z - ZB][k]);
+        for (int k = 0; k < P; ++k) o[k] = update(wb[y - 1][z - ZB][k], p.c0, g[k]);
       }
       if (p.flag) {
         bool bad = false;
@@ -390,7 +405,7 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
         write_row_digits<P, S>(o, ucnt, x, row, p, kp);
         if (p.drow1) {   // base1 is u or null (checked at launch)
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], p.base1 ? uc[k] : 0.0);
+          for (int k = 0; k < P; ++k) o[k] = (p.base1 ? uc[k] : 0.0) + p.c1 * g[k];
           write_row_digits<P, S>(o, ucnt, x, p.drow1 + row, p, kp);
         }
         continue;
@@ -405,11 +420,11 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
           for (int k = 0; k < P; ++k) o[k] = p.c1 * g[k];
         } else if (p.base1 == u) {
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], uc[k]);
+          for (int k = 0; k < P; ++k) o[k] = update(uc[k], p.c1, g[k]);
         } else {
           load_row<P>(o, p.base1, idx, nu, ucnt);
 #pragma unroll
-          for (int k = 0; k < P; ++k) o[k] = __builtin_fma(p.c1, g[k], o[k]);
+          for (int k = 0; k < P; ++k) o[k] += p.c1 * g[k];
         }
         if (p.out1f)
           store_row<P>(p.out1f, idxo, o, ucnt);
@@ -424,9 +439,9 @@ __device__ __forceinline__ void stencil_body(const StencilArgs& p, const Stencil
 // entry, so one compiled kernel serves both, and a problem's results do not depend on
 // whether it ran alone or in a group (two instantiations of the body may contract
 // multiply-adds differently, which changes last bits).
-template <int D, int P, int S>
+template <int D, int P, int S, int PAIR>
 __global__ __launch_bounds__(64 * SW, 3) void stencil_batch_kernel(StencilBatch b, StencilGrid sg) {
-  stencil_body<D, P, S>(b.a[blockIdx.y], sg);
+  stencil_body<D, P, S, PAIR>(b.a[blockIdx.y], sg);
 }
 
 // Points per lane: the P in {4, 2, 1} that pads n1 least to whole 64 P-point segments,
@@ -446,27 +461,31 @@ static int points_per_lane(int n1) {
   return best;
 }
 
-template <int D, int S>
+template <int D, int S, int PAIR>
 static void launch_batch_ds(int P, const StencilBatch& b, int count, StencilGrid sg, unsigned blocks,
                             hipStream_t s) {
   const dim3 grid(blocks, (unsigned)count);
   if (P == 4)
-    stencil_batch_kernel<D, 4, S><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
+    stencil_batch_kernel<D, 4, S, PAIR><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
   else if (P == 2)
-    stencil_batch_kernel<D, 2, S><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
+    stencil_batch_kernel<D, 2, S, PAIR><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
   else
-    stencil_batch_kernel<D, 1, S><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
+    stencil_batch_kernel<D, 1, S, PAIR><<<grid, dim3(64 * SW), 0, s>>>(b, sg);
 }
 
 template <int D>
 static void launch_batch_d(int P, const StencilBatch& b, int count, StencilGrid sg, unsigned blocks, hipStream_t s) {
   switch (b.a[0].dig ? b.a[0].dS : 0) {
-    case 3: launch_batch_ds<D, 3>(P, b, count, sg, blocks, s); break;
-    case 4: launch_batch_ds<D, 4>(P, b, count, sg, blocks, s); break;
-    case 5: launch_batch_ds<D, 5>(P, b, count, sg, blocks, s); break;
-    case 6: launch_batch_ds<D, 6>(P, b, count, sg, blocks, s); break;
-    case 7: launch_batch_ds<D, 7>(P, b, count, sg, blocks, s); break;
-    default: launch_batch_ds<D, 0>(P, b, count, sg, blocks, s); break;
+    case 3: launch_batch_ds<D, 3, 0>(P, b, count, sg, blocks, s); break;
+    case 4: launch_batch_ds<D, 4, 0>(P, b, count, sg, blocks, s); break;
+    case 5: launch_batch_ds<D, 5, 0>(P, b, count, sg, blocks, s); break;
+    case 6: launch_batch_ds<D, 6, 0>(P, b, count, sg, blocks, s); break;
+    case 7: launch_batch_ds<D, 7, 0>(P, b, count, sg, blocks, s); break;
+    default:
+      if (D == 3 && b.a[0].pair)
+        launch_batch_ds<D, 0, D == 3>(P, b, count, sg, blocks, s);
+      else
+        launch_batch_ds<D, 0, 0>(P, b, count, sg, blocks, s);
   }
 }
 
@@ -493,7 +512,12 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
   for (int i = 0; i < count; ++i)
     if (!a[i].u || !a[i].a || (!a[i].dig && !a[i].out0 && !a[i].out0f)) return hipErrorInvalidValue;
   for (int i = 1; i < count; ++i)   // one kernel for the group: the same output form
-    if ((a[i].dig != nullptr) != (a[0].dig != nullptr) || (a[0].dig && a[i].dS != a[0].dS))
+    if ((a[i].dig != nullptr) != (a[0].dig != nullptr) || (a[0].dig && a[i].dS != a[0].dS) || a[i].pair != a[0].pair)
+      return hipErrorInvalidValue;
+  // (the paired form: flux, Dirichlet ends, bases that are u or a stage)
+  for (int i = 0; i < count; ++i)
+    if (a[i].pair && (a[i].nondiv || a[i].dig || a[i].neu[0] || a[i].neu[1] || a[i].neu[2] ||
+                      (a[i].out1 && a[i].base1 != a[i].u)))
       return hipErrorInvalidValue;
   for (int i = 0; i < count; ++i)
     if (a[i].dig && (!a[i].dexp || a[i].dS < kMinSlices || a[i].dS > kMaxSlices || !stencil_row_in_one_wave(a[i].n1) ||
