@@ -92,7 +92,7 @@ def parse():
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_f64_255cube_l2b_counters.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_2303_15861_amd", "csrc", "contract.hip")
+KERNEL_SRC = os.path.join(ROOT, "paper_2303_15861_amd", "csrc", "regfac.hip")
 
 
 def measured_traffic():
@@ -104,7 +104,7 @@ def measured_traffic():
         text = open(TRAFFIC_FILE).read()
     except OSError:
         return None
-    m_sha = re.search(r"contract\.hip sha1: ([0-9a-f]{40})", text)
+    m_sha = re.search(r"regfac\.hip sha1: ([0-9a-f]{40})", text)
     m_bytes = re.search(r"traffic per launch \(bytes\): ([0-9.eE+]+)", text)
     if not m_sha or not m_bytes:
         return None

@@ -413,9 +413,9 @@ const double* folded(const mm_op* op, int mu, int j) {
 
 // (call with the launch's shape set). The grouped passes of one op (its φ1 quadrature
 // nodes and ERK stage groups) that the register-held kernel does not take fold when all
-// groups together have at least 512 folded tiles, whatever each group alone has; single launches follow the launcher's per-problem rule. The server's
-// grouped launches (group_pass) keep the per-problem rule: theirs must not depend on the
-// group count.
+// groups together have at least 512 folded tiles, whatever each group alone has; single
+// launches follow the launcher's per-problem rule. The server's grouped launches
+// (group_pass) keep the per-problem rule: theirs must not depend on the group count.
 void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
   g.ldf = (g.fold_blocks > 1 ? g.fold_blocks : 1) * fold_ld(op->n[mu]);
   g.fold = op->ctx ? op->ctx->fold : 1;

@@ -656,7 +656,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     load_a(ra, zs - 1, true);
     load_u(su1, zs, true);
     load_a(sa1, zs, true);
-    const __amdgpu_buffer_rsrc_t u2 = plane_of(p.u, (zs - 2) * su, su, zs >= 2), w1 = plane_of(p.base0, (zs - 1) * su, su, zs >= 1);
+    const __amdgpu_buffer_rsrc_t u2 = plane_of(p.u, (zs - 2) * su, su, zs >= 2);
+    const __amdgpu_buffer_rsrc_t w1 = plane_of(p.base0, (zs - 1) * su, su, zs >= 1);
     const __amdgpu_buffer_rsrc_t a2 = plane_of(p.a, (zs - 1) * sa, sa, zs >= 1), a1 = plane_of(p.a, zs * sa, sa, true);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -696,7 +697,8 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
     }
     __builtin_amdgcn_sched_barrier(0);
     const bool grid = z >= 0 && z < n3, out = z > zs, mine = z >= zs && z < ze;
-    const __amdgpu_buffer_rsrc_t o0 = plane_of(p.out0, (z - 1) * su, su, out), o1 = plane_of(p.out1, (z - 1) * su, su, out);
+    const __amdgpu_buffer_rsrc_t o0 = plane_of(p.out0, (z - 1) * su, su, out);
+    const __amdgpu_buffer_rsrc_t o1 = plane_of(p.out1, (z - 1) * su, su, out);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const double *a = A0 + ia[q], *u = U0 + iu[q];
