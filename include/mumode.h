@@ -271,7 +271,8 @@ mm_status mm_check(mm_ctx* ctx, const mm_op* op, void* stream);
  * launch's algorithmic work is recorded with it (mode products: 2*M*N*K flops per
  * batch, padding excluded; stencil: grid points). kind: MM_KIND_STENCIL, MM_KIND_GEMM_K
  * (mode-1 kernel, both operands read along k), MM_KIND_GEMM_N (modes 2..d, the grid
- * operand read along n) or MM_KIND_FUSED (whole small-2D solves, work = mode-product
+ * operand read along n) or MM_KIND_FUSED (whole small-2D solves, and launches of several
+ * products of an x3 slab or a periodic grid with their stage work; work = mode-product
  * flops). mm_timing_read synchronises the recorded events and returns
  * the totals since the last enable. */
 enum { MM_KIND_STENCIL = 0, MM_KIND_GEMM_K = 1, MM_KIND_GEMM_N = 2, MM_KIND_FUSED = 3 };
