@@ -541,19 +541,19 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
 // Between two Lawson2b steps in 3D, the last stage of one and the first of the next:
 //   u+ = W + c0 g(U),  out0 = u+ + c1 g(u+),  out1 = u+ + c0 g(u+),
 // without u+ ever going to memory: five passes over grid functions instead of eight, and each x3
-// plane read about once. A block takes W = 512 NQ - 2 n1 consecutive points of the (x1, x2) plane
+// plane read about once. A block takes W = TP NQ - 2 n1 consecutive points of the (x1, x2) plane
 // in row-major order (whatever the row length) and walks along x3 over zc planes. A thread owns NQ
-// points, 512 apart, of the run widened by one row on either side, where it computes u+; the
+// points, TP apart, of the run widened by one row on either side, where it computes u+; the
 // neighbours along x1 and x2 of U and a are read from LDS (two planes of each, loaded one
 // plane ahead), those of u+ likewise from LDS one plane later, and what lies along x3
-// (U, u+, faces) stays in the thread's registers. 255^3: 195 us against 2 x 119 for the two launches
+// (U, u+, faces) stays in the thread's registers. 255^3: 180 us against 2 x 119 for the two launches
 // (440 MB read, 290 MB written: not the traffic but about 120 vector instructions a point, 63 of
 // them arithmetic, and two barriers a plane bound it; loading two planes ahead gained nothing).
-// 127^3 32 against 2 x 17.5, 130 x 129 x 127 36 against 2 x 26.
+// 127^3 29 against 2 x 17.5, 130 x 129 x 127 33 against 2 x 26.
 // Every access to memory is a buffer access with the plane's size, at an offset past it where a
 // lane has nothing to load or store: no branch splits the loads in flight.
-constexpr int TP = 512;
-__host__ __device__ constexpr int pair_loads(int nq) { return nq + 2; }   // of a thread per run
+// loads of a thread per run
+__host__ __device__ constexpr int pair_loads(int tp, int nq) { return tp == 512 ? nq + 2 : nq + 1; }
 constexpr unsigned kNone = 0x80000000u;
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_of(const double* base, int64_t at, int64_t len, bool any) {
@@ -573,9 +573,9 @@ __host__ __device__ inline int run_elems(int w, int n1, int p) {
 }
 
 // PAD: the rows have padding, which is zero, so the x1 neighbours beyond their ends need no masks.
-template <int NQ, int PAD>
+template <int TP, int NQ, int PAD>
 __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(StencilBatch batch, int nruns, int zc) {
-  constexpr int NL = pair_loads(NQ);
+  constexpr int NL = pair_loads(TP, NQ);
   const StencilArgs& p = batch.a[blockIdx.y];
   extern __shared__ __attribute__((aligned(16))) double pair_lds[];
   const int n1 = p.n1, n2 = p.n2, n3 = p.n3, tid = threadIdx.x;
@@ -746,29 +746,37 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
   if (bad && p.flag) p.flag[0] = 1;
 }
 
-// The split of `count` grids: the NQ and the planes per block of the least estimated time, in
-// units of one point of every thread in one plane (a block's two extra planes and its start, about
-// two more; whole rounds of the blocks that the LDS lets run together). 0: not for this kernel.
-static double pair_split(const StencilArgs& a, int count, int& NQ, int& zc, size_t& lds) {
-  if (a.n1 < 2 || a.n3 < 2 || (int64_t)a.n1 * a.n2 > (1 << 24)) return 0.0;
+// The split of `count` grids: the block (tp threads of nq points) and the planes per block (zc) of
+// the least estimated time (us): whole rounds of the blocks that a compute unit holds together, each
+// of its planes, two extra ones and about two more for the start, at a measured time per plane and
+// point of 512 threads (unit). Four waves a SIMD cover each other's waits and barriers; larger blocks
+// compute fewer rows twice. Per step, (1024, 2) against 512 threads of four or five points:
+// 255^3 613 and 628 us, 160^3 163 and 170, 127^3 87 and 90.
+struct PairSplit {
+  int tp, nq, zc;
+  size_t lds;
+  double us;   // 0: not for this kernel
+};
+static PairSplit pair_split(const StencilArgs& a, int count) {
+  PairSplit best{};
+  if (a.n1 < 2 || a.n3 < 2 || (int64_t)a.n1 * a.n2 > (1 << 24)) return best;
   const int pu = a.ldi ? a.ldi : a.n1;
-  double best = 0.0;
-  for (int q = 1; q <= 5; ++q) {
-    const int R = TP * q, W = R - 2 * a.n1, Lu = run_elems(R, a.n1, pu), La = run_elems(R, a.n1, a.n1 + 2);
-    const size_t bytes = sizeof(double) * (3 * (size_t)Lu + 2 * La);
-    if (W < a.n1 || std::max(Lu, La) > TP * pair_loads(q) || bytes > 160 * 1024) continue;
-    const int occ = std::min<int>(160 * 1024 / bytes, q <= 2 ? 2 : 1);
+  constexpr struct {
+    int tp, nq;
+    double unit;
+  } kBlocks[] = {{512, 1, 0.63}, {512, 3, 0.68}, {1024, 1, 0.62}, {1024, 2, 0.52}};
+  for (const auto& k : kBlocks) {
+    const int tp = k.tp, q = k.nq;
+    const int R = tp * q, W = R - 2 * a.n1, Lu = run_elems(R, a.n1, pu), La = run_elems(R, a.n1, a.n1 + 2);
+    const size_t lds = sizeof(double) * (3 * (size_t)Lu + 2 * La);
+    if (W < a.n1 || std::max(Lu, La) > tp * pair_loads(tp, q) || lds > 160 * 1024) continue;
+    const int occ = std::min<int>(160 * 1024 / lds, q <= 2 ? 1024 / tp : 1);   // (registers: 16 or 8 waves)
+    const double unit = k.unit * occ * (tp / 512) * q;
     const int64_t runs = ((int64_t)a.n1 * a.n2 + W - 1) / W;
     for (int z = 2; z <= a.n3 && z <= 64; ++z) {
       const int64_t blocks = runs * ((a.n3 + z - 1) / z) * count;
-      const double rounds = (double)((blocks + 256 * occ - 1) / (256 * occ));
-      const double cost = rounds * occ * q * (z + 4);
-      if (best == 0.0 || cost < best) {
-        best = cost;
-        NQ = q;
-        zc = z;
-        lds = bytes;
-      }
+      const double us = (double)((blocks + 256 * occ - 1) / (256 * occ)) * unit * (z + 4);
+      if (best.us == 0.0 || us < best.us) best = {tp, q, z, lds, us};
     }
   }
   return best;
@@ -778,22 +786,20 @@ static bool pair_accepts(const StencilArgs& a) {
   return !a.nondiv && !a.sub && !a.dig && !a.out0f && !a.out1f && !a.neu[0] && !a.neu[1] && !a.neu[2] && a.ldi == a.ldo;
 }
 
-// Where the one launch is the faster: its estimate (0.7 us a unit: 3.5 us a plane measured for five)
-// against that of two launches of stencil_batch_kernel (7 ns per 1000 lanes, idle ones included),
+// Where the one launch is the faster: its estimate against that of two launches of stencil_batch_kernel (7 ns per 1000 lanes, idle ones included),
 // 3 us for each launch, and a margin for the estimates. Measured per step, two launches -> one: 63^3
-// 28.7 -> 31.3 us (stays), 96^3 56 -> 57 (stays), 110^3 81 -> 76, 127^3 95 -> 91, 130 x 129 x 127
-// 126 -> 108, 160^3 191 -> 171, 210^3 430 -> 375, 255^3 685 -> 627, 30 x 200 x 150 76 -> 64,
-// 200 x 30 x 150 67 -> 69 (stays).
+// 28.7 -> 29.0 us (stays), 96^3 56 -> 53.5, 110^3 81 -> 73, 127^3 95 -> 88.5, 130 x 129 x 127
+// 126 -> 106, 160^3 191 -> 162, 210^3 430 -> 359, 255^3 685 -> 614, 30 x 200 x 150 76 -> 63,
+// 200 x 30 x 150 67 -> 63.5.
 bool stencil_pair_pays(int d, const StencilArgs& a, int count) {
   if (d != 3 || !pair_accepts(a)) return false;
-  int NQ, zc, P;
-  size_t lds;
+  int P;
   StencilGrid sg;
   int64_t blocks;
-  const double cost = pair_split(a, count, NQ, zc, lds);
-  if (cost == 0.0 || !stencil_grid(d, a.n1, a.n2, a.n3, false, P, sg, blocks)) return false;
+  const double us = pair_split(a, count).us;
+  if (us == 0.0 || !stencil_grid(d, a.n1, a.n2, a.n3, false, P, sg, blocks)) return false;
   const double lanes = (double)blocks * (64 * SW) * P * 2 * count;
-  return 1.1 * (3.0 + 0.7 * cost) < 2.0 * (3.0 + 7e-6 * lanes);
+  return 1.1 * (3.0 + us) < 2.0 * (3.0 + 7e-6 * lanes);
 }
 
 hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s) {
@@ -805,20 +811,21 @@ hipError_t launch_stencil_pair(const StencilArgs* a, int count, hipStream_t s) {
       return hipErrorInvalidValue;
     b.a[i] = a[i];
   }
-  int NQ, zc;
-  size_t lds;
-  if (pair_split(a[0], count, NQ, zc, lds) == 0.0) return hipErrorInvalidValue;
-  const int W = TP * NQ - 2 * a[0].n1, nruns = (a[0].n1 * a[0].n2 + W - 1) / W;
-  const dim3 grid(((unsigned)nruns * (unsigned)((a[0].n3 + zc - 1) / zc) + 7) / 8 * 8, (unsigned)count);
-  auto go = [&](auto kernel) { kernel<<<grid, TP, lds, s>>>(b, nruns, zc); };
-  const bool pad = a[0].ldi > a[0].n1;
-  switch (NQ) {
-    case 1: pad ? go(stencil_pair_kernel<1, 1>) : go(stencil_pair_kernel<1, 0>); break;
-    case 2: pad ? go(stencil_pair_kernel<2, 1>) : go(stencil_pair_kernel<2, 0>); break;
-    case 3: pad ? go(stencil_pair_kernel<3, 1>) : go(stencil_pair_kernel<3, 0>); break;
-    case 4: pad ? go(stencil_pair_kernel<4, 1>) : go(stencil_pair_kernel<4, 0>); break;
-    default: pad ? go(stencil_pair_kernel<5, 1>) : go(stencil_pair_kernel<5, 0>); break;
-  }
+  const PairSplit sp = pair_split(a[0], count);
+  if (sp.us == 0.0) return hipErrorInvalidValue;
+  const int W = sp.tp * sp.nq - 2 * a[0].n1, nruns = (a[0].n1 * a[0].n2 + W - 1) / W;
+  const dim3 grid(((unsigned)nruns * (unsigned)((a[0].n3 + sp.zc - 1) / sp.zc) + 7) / 8 * 8, (unsigned)count);
+  auto go = [&](auto padded, auto plain) {
+    const auto kernel = a[0].ldi > a[0].n1 ? padded : plain;
+    kernel<<<grid, sp.tp, sp.lds, s>>>(b, nruns, sp.zc);
+  };
+  if (sp.tp == 1024)
+    sp.nq == 1 ? go(stencil_pair_kernel<1024, 1, 1>, stencil_pair_kernel<1024, 1, 0>)
+               : go(stencil_pair_kernel<1024, 2, 1>, stencil_pair_kernel<1024, 2, 0>);
+  else if (sp.nq == 1)
+    go(stencil_pair_kernel<512, 1, 1>, stencil_pair_kernel<512, 1, 0>);
+  else
+    go(stencil_pair_kernel<512, 3, 1>, stencil_pair_kernel<512, 3, 0>);
   return hipGetLastError();
 }
 

@@ -42,10 +42,11 @@ def problem(n, seed=61, steps=3):
                                 beta_bar=(0.5, -0.25, 0.0), lam=0.9, r=(0.1, 0.7, -0.4, 0.2))
 
 
-# (one to five points a thread; rows far shorter than a block's run and longer than a wave; an
-# odd last chunk of planes; the last two stay two launches)
+# (blocks of 512 and 1024 threads, one to three points each; rows far shorter than a block's run and longer than a wave; an
+# odd last chunk of planes; the last three stay two launches)
 @pytest.mark.parametrize("n", [(2, 65, 128), (3, 301, 30), (17, 129, 65), (33, 200, 97), (65, 66, 67), (65, 129, 65),
-                               (129, 200, 33), (257, 200, 15), (256, 30, 200), (257, 400, 15), (31, 33, 2), (48, 50, 1)])
+                               (129, 200, 33), (257, 200, 15), (256, 30, 200), (257, 400, 15), (490, 200, 15),
+                               (31, 33, 2), (48, 50, 1)])
 def test_run_matches_single_steps_and_oracle(mm, n):
     p = problem(n)
     (got,), st = solve(mm, [p], True)
