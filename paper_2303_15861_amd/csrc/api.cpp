@@ -1730,7 +1730,7 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
     // them with x1 rows padded to whole 128-byte lines (16 values) from n1 = 32 on: rows
     // of n1 = 255 values start 2040 bytes apart, so most rows begin and end inside a
     // line, and the mode products read and write partial lines. The padding is zeroed
-    // here and stays zero (no pass writes it except with products of zeros).
+    // here, but exponential actions use the buffers unpadded: nothing relies on its values.
     op->ld1 = op->n[0];
     if (!periodic && (scheme == MM_LAWSON_EULER || scheme == MM_LAWSON2B) && op->n[0] >= 32)
       op->ld1 = (op->n[0] + 15) / 16 * 16;

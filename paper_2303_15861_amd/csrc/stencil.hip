@@ -572,7 +572,8 @@ __host__ __device__ inline int run_elems(int w, int n1, int p) {
   return ((w - 1) / n1 + 1) * (p - n1) + w + 2 * p + 4;
 }
 
-// PAD: the rows have padding, which is zero, so the x1 neighbours beyond their ends need no masks.
+// PAD: the rows have padding, which is loaded as zero (whatever it holds: exponential actions use
+// the same scratch unpadded), so the x1 neighbours beyond their ends need no masks.
 template <int TP, int NQ, int PAD>
 __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(StencilBatch batch, int nruns, int zc) {
   constexpr int NL = pair_loads(TP, NQ);
@@ -603,13 +604,16 @@ __global__ __launch_bounds__(TP, NQ <= 2 ? 4 : 2) void stencil_pair_kernel(Stenc
 
   const double lam = p.lam_amax;
   // (a plane outside the grid, or not wanted: zeros)
+  unsigned uoff[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int k = tid + TP * i;
+    uoff[i] = k < lu && (!PAD || (u0 + k) % pu < n1) ? 8u * (unsigned)(u0 + k) : kNone;
+  }
   auto load_u = [&](double (&ru)[NL], int z, bool any) {
     const __amdgpu_buffer_rsrc_t r = plane_of(p.u, z * su, su, any && z >= 0 && z < n3);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int k = tid + TP * i;
-      ru[i] = plane_load(r, k < lu ? 8u * (unsigned)(u0 + k) : kNone);
-    }
+    for (int i = 0; i < NL; ++i) ru[i] = plane_load(r, uoff[i]);
   };
   auto load_a = [&](double (&ra)[NL], int z, bool any) {   // -1 <= z <= n3
     const __amdgpu_buffer_rsrc_t r = plane_of(p.a, (z + 1) * sa, sa, any);

@@ -68,3 +68,19 @@ def test_nonfinite_state_is_flagged(mm):
     p.u0 = p.u0.copy()
     p.u0[10, 4, 3] = np.inf
     assert solve(mm, [p], True)[1] == [mm.MM_EUNSTABLE]
+
+
+def test_run_after_an_action_on_the_same_operator(mm):
+    """An exponential action leaves its unpadded intermediates in the operator's scratch, also where
+    the stage vectors have their row padding."""
+    import torch
+    p = problem((129, 200, 33))
+    (ref,), _ = solve(mm, [p], True)
+    ctx = mm.Context(0)
+    op = mm.setup_problem(ctx, p)
+    u = torch.from_numpy(np.ascontiguousarray(p.u0)).cuda()
+    mm.mumode_expv(op, torch.full_like(u, 7.0), torch.empty_like(u))
+    mm.step(op, u, p.steps)
+    assert np.array_equal(u.cpu().numpy(), ref)
+    op.close()
+    ctx.close()
