@@ -296,8 +296,8 @@ hipError_t launch_gemm_sliced_chain(ChainArgs& c, hipStream_t s);
 hipError_t launch_slice_rows(signed char* dst, int* exps, const double* src, int rows, int k, int lds, int ldd,
                              int S, hipStream_t s);
 hipError_t launch_stencil(int d, const StencilArgs& a, hipStream_t s);
-// count (1..kMaxGroups) problems with equal n1, n2, n3 in one launch; each problem's
-// outputs are bit-identical to launch_stencil's.
+// count (1..kMaxGroups) problems with equal n1, n2, n3 in one launch (two where only some have
+// the paired arithmetic); each problem's outputs are bit-identical to launch_stencil's.
 hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStream_t s);
 // The last stage of a Lawson2b step and the first of the next at once (3D, FP64, flux form,
 // Dirichlet ends, equal row strides ldi = ldo): u+ = base0 + c0 g(u), out0 = u+ + c1 g(u+),

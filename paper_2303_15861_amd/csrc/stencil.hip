@@ -512,8 +512,22 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
   for (int i = 0; i < count; ++i)
     if (!a[i].u || !a[i].a || (!a[i].dig && !a[i].out0 && !a[i].out0f)) return hipErrorInvalidValue;
   for (int i = 1; i < count; ++i)   // one kernel for the group: the same output form
-    if ((a[i].dig != nullptr) != (a[0].dig != nullptr) || (a[0].dig && a[i].dS != a[0].dS) || a[i].pair != a[0].pair)
+    if ((a[i].dig != nullptr) != (a[0].dig != nullptr) || (a[0].dig && a[i].dS != a[0].dS))
       return hipErrorInvalidValue;
+  for (int i = 1; i < count; ++i) {
+    if (!a[i].pair == !a[0].pair) continue;
+    // problems with and without the paired arithmetic (flux form with Dirichlet ends, and others):
+    // a launch each, so that every problem keeps the arithmetic it has alone
+    StencilArgs part[kMaxGroups];
+    for (int pair = 0; pair < 2; ++pair) {
+      int m = 0;
+      for (int k = 0; k < count; ++k)
+        if (!a[k].pair == !pair) part[m++] = a[k];
+      const hipError_t e = launch_stencil_batch(d, part, m, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   // (the paired form: flux, Dirichlet ends, bases that are u or a stage)
   for (int i = 0; i < count; ++i)
     if (a[i].pair && (a[i].nondiv || a[i].dig || a[i].neu[0] || a[i].neu[1] || a[i].neu[2] ||
