@@ -2609,10 +2609,28 @@ hipError_t group_pass(mm_ctx* ctx, const mm_op* const* ops, int count, int mu, i
     g.vdig_cap = ws->vdig_cap;
     g.vexp_cap = ws->vexp_cap;
   }
+  auto launch_part = [&](GemmArgs& h) {
+    const double work = gemm_work(h, o0->prec);
+    return timed_launch(ctx, h.b_trans ? MM_KIND_GEMM_N : MM_KIND_GEMM_K, work, s,
+                        [&] { return launch_gemm(o0->prec, h, s); });
+  };
+  // A launch folds only if every problem in it has a folded factor on this axis. Where some have
+  // none (advection in A, a Neumann end) and the others' products fold, each kind gets a launch, so
+  // that every problem takes the product that it takes alone.
   auto launch = [&]() {
-    const double work = gemm_work(g, o0->prec);
-    return timed_launch(ctx, g.b_trans ? MM_KIND_GEMM_N : MM_KIND_GEMM_K, work, s,
-                        [&] { return launch_gemm(o0->prec, g, s); });
+    GemmArgs part[2] = {g, g};   // without and with a folded factor
+    part[0].groups = part[1].groups = 0;
+    for (int i = 0; i < count; ++i) {
+      GemmArgs& h = part[g.Ff[i] != nullptr];
+      const int k = h.groups++;
+      h.A[k] = g.A[i];
+      h.B[k] = g.B[i];
+      h.C[k] = g.C[i];
+      h.Ff[k] = g.Ff[i];
+    }
+    if (!part[0].groups || !part[1].groups || !use_fold(part[1], o0->prec)) return launch_part(g);
+    const hipError_t e = launch_part(part[1]);
+    return e == hipSuccess ? launch_part(part[0]) : e;
   };
   if (mu == 0) {
     g.M = (int)(dof / n) * nvec;

@@ -59,7 +59,10 @@ def run(mm, probs, steps):
 
 @pytest.mark.parametrize("n,scheme,kinds", [((16, 12, 9), "l2b", ALL),
                                             ((20, 18, 16), "l2b", ("plain", "nondiv", "plain")),
-                                            ((96, 96, 96), "l2b", ("plain", "nondiv"))])
+                                            ((96, 96, 96), "l2b", ("plain", "nondiv")),
+                                            ((33, 34, 35), "l2b", ALL), ((40, 5, 63), "le", ALL), ((17, 16, 70), "l2b", ALL),
+                                            ((90, 70), "l2b", ALL), ((130, 70), "le", ALL),
+                                            ((129, 130, 40), "l2b", ("advected", "plain"))])
 @pytest.mark.parametrize("reverse", [False, True])
 def test_mixed_group_equals_alone(mm, n, scheme, kinds, reverse):
     probs = forms(n, kinds[::-1] if reverse else kinds, scheme)
@@ -86,7 +89,7 @@ def serve(mm, batch):
         srv.close()
 
 
-@pytest.mark.parametrize("kinds", [("plain", "nondiv", "nondiv", "plain")])
+@pytest.mark.parametrize("kinds", [("plain", "nondiv", "nondiv", "plain"), ALL])
 def test_server_mixes_forms(mm, kinds):
     """Requests of one class and different forms, long enough to be advanced together: each equals
     the same request served alone."""
