@@ -2862,7 +2862,7 @@ mm_status enqueue_small2d_group(mm_ctx* ctx, const mm_op* const* ops, double* co
   double work = 0.0;
   for (int i = 0; i < count; ++i) {
     const mm_op* op = ops[i];
-    if ((op->scheme == MM_LAWSON2B) != l2b) return MM_EINVAL;
+    if ((op->scheme == MM_LAWSON2B) != l2b || !small2d_fusable(ctx, op)) return MM_EINVAL;
     args[i] = small_args(op, u[i], nsteps[i]);
     work += small_work(op, args[i]);
   }
@@ -2905,12 +2905,26 @@ mm_status lawson_step_batch(mm_ctx* ctx, const mm_op* const* ops, double* const*
   }
   if (nsteps == 0) return MM_OK;
   hipStream_t s = (hipStream_t)stream;
-  if (small2d_fusable(ctx, ops[0])) {
-    int ns[kMaxGroups];
-    for (int i = 0; i < count; ++i) ns[i] = nsteps;
-    return enqueue_small2d_group(ctx, ops, u, ns, count, s);
+  // (one class: small 2D problems of the one-workgroup solver next to others of a form that it
+  // does not have)
+  const mm_op *small[kMaxGroups], *rest[kMaxGroups];
+  double *us[kMaxGroups], *ur[kMaxGroups];
+  int ns[kMaxGroups], nsmall = 0, nrest = 0;
+  for (int i = 0; i < count; ++i) {
+    if (small2d_fusable(ctx, ops[i])) {
+      small[nsmall] = ops[i];
+      us[nsmall] = u[i];
+      ns[nsmall++] = nsteps;
+    } else {
+      rest[nrest] = ops[i];
+      ur[nrest++] = u[i];
+    }
   }
-  return enqueue_lawson_group(ctx, ops, u, count, nsteps, s);
+  if (nsmall) {
+    mm_status rc = enqueue_small2d_group(ctx, small, us, ns, nsmall, s);
+    if (rc != MM_OK) return rc;
+  }
+  return nrest ? enqueue_lawson_group(ctx, rest, ur, nrest, nsteps, s) : MM_OK;
 }
 
 }  // extern "C"

@@ -4,7 +4,8 @@ problem of such a group gives the bits of lawson_step on it alone, whatever its 
 their order, in lawson_step_batch and in the request server.
 
 Sizes: axes below and above the first folded length (17), grids whose Lawson2b stages run in
-pairs (96^3)."""
+pairs (96^3), 2D grids of the one-workgroup solver (which has the flux form with Dirichlet ends
+only) and beyond it."""
 import dataclasses
 import time
 
@@ -62,7 +63,9 @@ def run(mm, probs, steps):
                                             ((96, 96, 96), "l2b", ("plain", "nondiv")),
                                             ((33, 34, 35), "l2b", ALL), ((40, 5, 63), "le", ALL), ((17, 16, 70), "l2b", ALL),
                                             ((90, 70), "l2b", ALL), ((130, 70), "le", ALL),
-                                            ((129, 130, 40), "l2b", ("advected", "plain"))])
+                                            ((129, 130, 40), "l2b", ("advected", "plain")),
+                                            ((40, 33), "l2b", ALL), ((63, 16), "le", ALL),
+                                            ((64, 5), "l2b", ("plain", "neumann"))])
 @pytest.mark.parametrize("reverse", [False, True])
 def test_mixed_group_equals_alone(mm, n, scheme, kinds, reverse):
     probs = forms(n, kinds[::-1] if reverse else kinds, scheme)
