@@ -412,15 +412,17 @@ const double* folded(const mm_op* op, int mu, int j) {
 }
 
 // (call with the launch's shape set). The grouped passes of one op (its φ1 quadrature
-// nodes and ERK stage groups) that the register-held kernel does not take fold when all
-// groups together have at least 512 folded tiles, whatever each group alone has; single
-// launches follow the launcher's per-problem rule. The server's grouped launches
-// (group_pass) keep the per-problem rule: theirs must not depend on the group count.
+// nodes and ERK stage groups) take the register-held kernel where all groups' fibers together
+// are enough for it, and fold otherwise when all groups together have at least 512 folded
+// tiles, whatever each group alone has; single launches follow the launcher's per-problem
+// rule. The server's grouped launches (group_pass) keep the per-problem rule: theirs must
+// not depend on the group count.
 void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
   g.ldf = (g.fold_blocks > 1 ? g.fold_blocks : 1) * fold_ld(op->n[mu]);
   g.fold = op->ctx ? op->ctx->fold : 1;
   if (g.fold == 1 && io.few_plain) g.fold = 3;
-  if (g.fold == 1 && g.groups > 1 && !fold_regs_fits(g)) g.fold = fold_tiles(g) * g.groups >= 512 ? 2 : 0;
+  if (g.fold == 1 && g.groups > 1)
+    g.fold = fold_regs_pays(g, g.groups) || fold_tiles(g) * g.groups >= 512 ? 2 : 0;
 }
 
 // the stacked last-axis factor of an ERK stage in the op's precision

@@ -973,13 +973,13 @@ hipError_t launch_fold(GemmArgs& g, hipStream_t s) {
 // 256 points, stacked factors) take over from the plain ones from this many 128 x 64 tiles per group: at 127^3
 // Lawson2b (254 tiles per pass) the tiled folded step runs 109 against 121 us, while a
 // single 127^3 vector (127 tiles) runs faster on the plain kernel's 64-tiles, which spread
-// it over more compute units. The register-held kernel is the faster one from 17 points on,
-// however few the fibers: its workgroups need no 128 of them (batches of eight 63^3
+// it over more compute units. The register-held kernel is the faster one from 17 points on, where
+// its own rule (fold_regs_pays) says so: its workgroups need no 128 fibers (batches of eight 63^3
 // Lawson2b: products 17 us each against 21-49 plain, 31^3: 4.4-4.7 against 4.7-5.4).
 constexpr int64_t kFoldMinTiles = 192;
 
 // Whether g runs folded: FP64, every group with a folded factor, a square factor, and
-// (fold = 1) within the register-held kernel's limits or (fold = 1 or 3) at least
+// (fold = 1) the register-held kernel is the faster one or (fold = 1 or 3) at least
 // kFoldMinTiles tiles per group.
 // The count excludes the group count, so that a problem's products take the same form
 // alone and in a grouped launch with other problems (folded and plain products round
@@ -995,7 +995,7 @@ bool use_fold(const GemmArgs& g, int prec) {
   if (g.K % G != 0 || (g.b_trans ? g.M : g.N) != g.K / G || (G > 1 && !g.b_trans)) return false;
   for (int i = 0; i < g.groups; ++i)
     if (!g.Ff[i]) return false;
-  return g.fold == 2 || (g.fold == 1 && fold_regs_fits(g)) || fold_tiles(g) >= kFoldMinTiles;
+  return g.fold == 2 || (g.fold == 1 && fold_regs_pays(g, 1)) || fold_tiles(g) >= kFoldMinTiles;
 }
 
 hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s) {

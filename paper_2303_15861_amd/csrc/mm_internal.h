@@ -250,6 +250,9 @@ int64_t fold_tiles(const GemmArgs& g);
 // does not fill the chip), for modes 2/3 at least two columns, and operands below 2 GB
 // (32-bit byte offsets).
 bool fold_regs_fits(const GemmArgs& g);
+// Whether g, with `groups` problems' fibers counted, has enough fibers for it to be faster than the
+// plain product.
+bool fold_regs_pays(const GemmArgs& g, int groups);
 hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s);
 // Plain FP64 products of the same kind, square factors of at most 64 points.
 bool plain_regs_fits(const GemmArgs& g);

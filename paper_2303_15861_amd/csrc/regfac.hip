@@ -572,11 +572,11 @@ hipError_t launch_plain_regs(GemmArgs& g, hipStream_t s) {
   return g.b_trans ? launch_plain_bt<1>(g, s) : launch_plain_bt<0>(g, s);
 }
 
-// Up to 128 folded positions the register-held kernel is the faster one at every size. Beyond,
-// with one wave per SIMD, it wins where the tiled kernel's 128 x 64 tiles do not fill the
-// chip (512 of them): two 511 x 511 vectors 14.5 us per product against 22-24 (plain
-// 32-tiles), but 383^3 in unpadded rows 430-495 us against 480-505 alone and 5% behind in
-// the ETD2RK step.
+// Up to 128 folded positions the register-held kernel is a faster folded one than the tiled
+// kernel at every size. Beyond, with one wave per SIMD, it wins where the tiled kernel's
+// 128 x 64 tiles do not fill the chip (512 of them): two 511 x 511 vectors 14.5 us per
+// product against 22-24 (plain 32-tiles), but 383^3 in unpadded rows 430-495 us against
+// 480-505 alone and 5% behind in the ETD2RK step.
 constexpr int64_t kWideMaxTiles = 512;
 
 bool fold_regs_fits(const GemmArgs& g) {
@@ -586,6 +586,27 @@ bool fold_regs_fits(const GemmArgs& g) {
   return offsets_fit(g);
 }
 
-hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s) { return g.b_trans ? launch_fold_bt<1>(g, s) : launch_fold_bt<0>(g, s); }
+// Where it is the faster one than the plain product. On few units of 16 fibers either kernel is a
+// single round of workgroups, and time is a workgroup's own: its factor rows, its first tile and
+// its chain. Up to 64 folded positions (and beyond 128: row groups of four waves) the
+// register-held kernel is no slower then; with five or six row tiles it takes 10.4-11 us at 144 points
+// and 13 at 176 against 10 and 11 of the plain one, until the latter needs further rounds (12.5 and
+// 14.3 us at 256 units); with seven or eight 11-12.6 against 12-13.4. Factor rows a multiple of 128
+// bytes apart take it another 3-4 us to load (160 points 14.1 against 10.5 us, 191 17.6 against 11.4,
+// 224 13.7 against 12.4, 255 16 against 13.1).
+constexpr int64_t kNarrowUnits = 192, kNarrowAlignedUnits = 352, kAlignedUnits = 160;
+
+bool fold_regs_pays(const GemmArgs& g, int groups) {
+  if (!fold_regs_fits(g)) return false;
+  const int f = g.K - g.K / 2;
+  if (f <= 64 || f > 128) return true;
+  const bool aligned = fold_ld(g.K) % 16 == 0;
+  const int64_t least = f <= 96 ? (aligned ? kNarrowAlignedUnits : kNarrowUnits) : aligned ? kAlignedUnits : 0;
+  return ((int64_t)((g.b_trans ? g.N : g.M) + 15) / 16) * g.inner * groups >= least;
+}
+
+hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s) {
+  return g.b_trans ? launch_fold_bt<1>(g, s) : launch_fold_bt<0>(g, s);
+}
 
 }  // namespace mm
