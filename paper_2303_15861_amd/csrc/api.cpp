@@ -365,6 +365,7 @@ struct PassIO {
   bool in_f32 = false, out_f32 = false;
   bool ready = false;   // MM_SLICED mode 1: the grid operand is already split (by the stencil)
   bool few_plain = false;   // FP64: launches of few folded tiles stay plain (GemmArgs::fold = 3)
+  bool chunked_next = false;   // GemmArgs::chunked_next
 };
 
 // Low-precision modes pass FP32 values between the passes of an action.
@@ -425,6 +426,25 @@ void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
     g.fold = fold_regs_pays(g, g.groups) || fold_tiles(g) * g.groups >= 512 ? 2 : 0;
 }
 
+// Whether the product of nvec stacked vectors along axis mu >= 1 (factor j, rows of ld values) is
+// one of the tiled kernels (FP64): longer than the register-held plain kernel takes, and not on
+// the register-held folded one
+bool chunked(const mm_op* op, int mu, int j, int nvec, int ld, bool few_plain) {
+  if (op->prec != MM_FP64 || op->n[mu] <= 64) return false;
+  const bool last = mu == last_axis(op);
+  GemmArgs g{};
+  g.Ff[0] = folded(op, mu, j);
+  g.M = g.K = g.lda = op->n[mu];
+  g.N = op->d == 3 && last ? op->n[1] * ld : op->n[0];
+  g.ldb = g.ldc = op->d == 3 && last ? g.N : ld;
+  g.inner = last ? nvec : nvec * op->n[2];
+  g.sB = g.sC = (int64_t)g.M * g.ldb;
+  g.groups = 1;
+  g.b_trans = 1;
+  g.fold = !op->ctx ? 1 : op->ctx->fold == 1 && few_plain ? 3 : op->ctx->fold;
+  return !(use_fold(g, MM_FP64) && fold_regs_fits(g));
+}
+
 // the stacked last-axis factor of an ERK stage in the op's precision
 const void* stacked(const mm_op* op, int which) {
   if (op->prec == MM_FP64) return which == 1 ? op->f3_stage1 : which == 2 ? op->f3_stage2 : op->f3_phi;
@@ -478,6 +498,7 @@ hipError_t pass_mode1(const mm_op* op, int groups, const void* const* in, const 
   g.fac_slice = factor_slice_stride(op, n1, n1);
   g.vready = io.ready;
   set_fold(op, g, 0, io);
+  g.chunked_next = io.chunked_next;
   return gemm(op, g, s);
 }
 
@@ -513,6 +534,7 @@ hipError_t pass_mode2(const mm_op* op, int groups, const int* fidx, const void* 
   g.out_f32 = io.out_f32;
   g.fac_slice = factor_slice_stride(op, op->n[1], op->n[1]);
   set_fold(op, g, 1, io);
+  g.chunked_next = io.chunked_next;
   return gemm(op, g, s);
 }
 
@@ -631,6 +653,9 @@ hipError_t exp_action(const mm_op* op, int j, const void* in, bool in_f32, doubl
   const int la = last_axis(op);
   const void* Fl = factor_op(op, la, j);
   const int* Fe = factor_exp(op, la, j);
+  const int ldt = lt.ld ? lt.ld : op->n[0];
+  first.chunked_next = chunked(op, 1, j, nvec, ldt, few_plain);
+  if (op->d == 3) mid.chunked_next = chunked(op, 2, j, nvec, ldt, few_plain);
   if (op->d == 3) {
     hipError_t e = pass_mode1(op, 1, i1, fj, o1, (int)(op->dof / op->n[0]) * nvec, first, s, nullptr, li, lt);
     if (e != hipSuccess) return e;
@@ -666,7 +691,10 @@ hipError_t grouped_action(const mm_op* op, int G, const double* const* ins, cons
     in1[g] = ins[g];
     o1[g] = (char*)t0 + g * op->dof * esz;
   }
-  hipError_t e = pass_mode1(op, G, in1, fidx, o1, (int)(op->dof / op->n[0]), PassIO{false, mixed}, s, w1);
+  PassIO first{false, mixed}, mid{mixed, mixed};
+  first.chunked_next = op->d == 2 || chunked(op, 1, fidx[0], G, op->n[0], false);
+  mid.chunked_next = true;   // (the stacked last product)
+  hipError_t e = pass_mode1(op, G, in1, fidx, o1, (int)(op->dof / op->n[0]), first, s, w1);
   if (e != hipSuccess) return e;
   if (op->d == 3) {
     const void* i2[kMaxGroups];
@@ -675,7 +703,7 @@ hipError_t grouped_action(const mm_op* op, int G, const double* const* ins, cons
       i2[g] = (const char*)t0 + g * op->dof * esz;
       o2[g] = (char*)t1 + g * op->dof * esz;
     }
-    e = pass_mode2(op, G, fidx, i2, o2, op->n[2], PassIO{mixed, mixed}, s);
+    e = pass_mode2(op, G, fidx, i2, o2, op->n[2], mid, s);
     if (e != hipSuccess) return e;
     return pass_last(op, F3, F3exp, G, t1, out, add, 1.0, beta, 1, PassIO{mixed, false}, s, Layout{0, 0},
                      Layout{0, 0}, F3fold);
@@ -2605,6 +2633,8 @@ hipError_t group_pass(mm_ctx* ctx, const mm_op* const* ops, int count, int mu, i
   g.vready = io.ready;
   g.ldf = fold_ld(n);
   g.fold = ctx->fold;
+  for (int i = 0; i < count && mu + 1 < d; ++i)
+    if (chunked(ops[i], mu + 1, 0, nvec, lo.ld, false)) g.chunked_next = 1;
   if (ws) {
     g.vdig = ws->vdig;
     g.vexp = ws->vexp;

@@ -61,8 +61,10 @@ struct GemmArgs {
   // each block centrosymmetric; the grid operand stacks as many vectors), folded block by
   // block side by side (launch_fold_stacked; ldf = fold_blocks fold_ld(n)); 0 or 1: one
   int fold_blocks;
+  int chunked_next;     // the output is next read by a tiled product (FP64)
   // filled by the launcher
   int tiles_m, tiles_n, total, per_xcd;
+  int stream_out;
 };
 
 constexpr int kFacPad = 32;   // k padding of pre-converted factors

@@ -54,8 +54,9 @@ __device__ __forceinline__ d2 load2(__amdgpu_buffer_rsrc_t r, unsigned off, unsi
 __device__ __forceinline__ double load1(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, uniform, 0));
 }
+template <bool NT>
 __device__ __forceinline__ void store1(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform, double v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, uniform, 2 /* nontemporal */);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, uniform, NT ? 2 /* nontemporal */ : 0);
 }
 
 // position of the k pair (2u, 2u + 1) in an LDS row, in pairs: a lane group reads its pair
@@ -288,14 +289,16 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
     return live && (whole_rows || (BT ? r0 + 4 * t + lg : r0 + lr) < m) ? o1 : kOut;
   };
   // element t of unit j of y to C (alpha = 1, nothing added)
-  auto write = [&](const d4 (&y)[NS][NC], int j, int t) {
+  auto write = [&](const d4 (&y)[NS][NC], int j, int t, auto stream) {
+    constexpr bool NT = decltype(stream)::value;
     const double a = y[0][j][t], b = FOLD ? y[NS - 1][j][t] : 0.0;
-    store1(cr, lane0(j, t), rb[j] + t * st, FOLD ? a + b : a);
-    if (FOLD) store1(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, a - b);
+    store1<NT>(cr, lane0(j, t), rb[j] + t * st, FOLD ? a + b : a);
+    if (FOLD) store1<NT>(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, a - b);
   };
   // the tile's results with alpha and the added term (all its loads in flight together; a load
   // at kOut gives zero)
-  auto write_scaled = [&]() {
+  auto write_scaled = [&](auto stream) {
+    constexpr bool NT = decltype(stream)::value;
     const double alpha = p.alpha, beta = p.beta;
     double x[NC][4][NS];
 #pragma unroll
@@ -314,8 +317,8 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
       for (int t = 0; t < 4; ++t) {
         const double a = acc[0][j][t], b = FOLD ? acc[NS - 1][j][t] : 0.0;
         const double y0 = alpha * (FOLD ? a + b : a), y1 = alpha * (a - b);
-        store1(cr, lane0(j, t), rb[j] + t * st, Cadd ? y0 + beta * x[j][t][0] : y0);
-        if (FOLD) store1(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, Cadd ? y1 + beta * x[j][t][NS - 1] : y1);
+        store1<NT>(cr, lane0(j, t), rb[j] + t * st, Cadd ? y0 + beta * x[j][t][0] : y0);
+        if (FOLD) store1<NT>(cr, lane1(j, t), rb[j] + (BT ? 3 - t : t) * st, Cadd ? y1 + beta * x[j][t][NS - 1] : y1);
       }
   };
 
@@ -421,12 +424,18 @@ __global__ __launch_bounds__(64 * RW * WC, WPE) void gemm_f64_regs(GemmArgs p) {
     results_of_tile();
   };
   auto write_all = [&]() {
-    if (!plain_out) {
-      write_scaled();
-    } else {
+    auto go = [&](auto stream) {
+      if (!plain_out) {
+        write_scaled(stream);
+      } else {
 #pragma unroll
-      for (int r = 0; r < 4 * NC; ++r) write(acc, r / 4, r % 4);
-    }
+        for (int r = 0; r < 4 * NC; ++r) write(acc, r / 4, r % 4, stream);
+      }
+    };
+    if (p.stream_out)
+      go(std::true_type{});
+    else
+      go(std::false_type{});
   };
   int u0 = w * CT;
   if (LATE && ((wave >> 2) & 1)) {
@@ -473,6 +482,13 @@ struct Shape {
   static constexpr int LATE = RT >= 5 && RT <= 8;
 };
 
+// Outputs are stored past the caches, except small ones that a tiled product reads next: on few
+// tiles its chain of K chunks waits for each load. Along 2700 points after 65 (1.4 MB) it takes
+// 98 us on cached values and 118 on streamed ones; along 4000 after 176 (5.6 MB) the Lawson-Euler
+// step takes 188 and 206. Large outputs gain nothing from the caches (255^3 Lawson2b steps 635 us
+// streamed, 647 cached).
+constexpr int64_t kCachedBytes = 6 << 20;
+
 template <int BT, int FOLD, int H>
 hipError_t launch_regs_h(GemmArgs& g, hipStream_t s) {
   typedef Shape<FOLD, H> S;
@@ -492,6 +508,7 @@ hipError_t launch_regs_h(GemmArgs& g, hipStream_t s) {
   g.tiles_n = (int)W;
   g.total = (int)(RG * W * g.groups);
   g.per_xcd = (g.total + 7) / 8;
+  g.stream_out = !g.chunked_next || 8 * units * 16 * n * g.groups > kCachedBytes;
   gemm_f64_regs<BT, FOLD, H, S::RW, S::WC, S::NC, S::WPE, S::LATE><<<dim3(8 * g.per_xcd), dim3(64 * S::RW * S::WC), 0, s>>>(g);
   return hipGetLastError();
 }
