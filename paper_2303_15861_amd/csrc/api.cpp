@@ -412,6 +412,9 @@ const double* folded(const mm_op* op, int mu, int j) {
   return op->ffold[mu] + (int64_t)j * 2 * f * fold_ld(op->n[mu]);
 }
 
+// The fold mode of a grouped pass of one op under the default one (below)
+int group_fold(const GemmArgs& g) { return fold_regs_pays(g, g.groups) || fold_tiles(g) * g.groups >= 512 ? 2 : 0; }
+
 // (call with the launch's shape set). The grouped passes of one op (its φ1 quadrature
 // nodes and ERK stage groups) take the register-held kernel where all groups' fibers together
 // are enough for it, and fold otherwise when all groups together have at least 512 folded
@@ -422,8 +425,7 @@ void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
   g.ldf = (g.fold_blocks > 1 ? g.fold_blocks : 1) * fold_ld(op->n[mu]);
   g.fold = op->ctx ? op->ctx->fold : 1;
   if (g.fold == 1 && io.few_plain) g.fold = 3;
-  if (g.fold == 1 && g.groups > 1)
-    g.fold = fold_regs_pays(g, g.groups) || fold_tiles(g) * g.groups >= 512 ? 2 : 0;
+  if (g.fold == 1 && g.groups > 1) g.fold = group_fold(g);
 }
 
 // Whether the product of nvec stacked vectors along axis mu >= 1 (factor j, rows of ld values) is
@@ -777,6 +779,63 @@ hipError_t sine_pass(const mm_op* op, bool inverse, int mu, int groups, const do
     g.sB = g.sC = (int64_t)n * g.N;
   }
   return gemm(op, g, s);
+}
+
+// Whether the sine basis is the faster form of op's steps, from the estimated times of the mode
+// products and scalings of either (the stencils are the same). It has twice the launches of the
+// grouped node products (an ETD2RK step in 3D 12 products and two scalings against 6 products), and
+// always the work of 15 products of one vector, against 3 (2q + 1): small grids and few nodes stay
+// with the products of exponentials (ETD2RK q = 4: 31^3 47 us against 79, 63^3 77 against 92; 95^3 188
+// against 167, 127^3 319 against 249 in the sine basis; q = 1 151 against 249). With exact functions
+// both forms have the same products, folded here and plain there (255^2 114 us plain against 136,
+// 31^3 64 against 77; 72^3 141 against 110 folded). phi1 actions break even at nearly the same
+// sizes and nodes as steps and follow them.
+bool sine_pays(const mm_op* op) {
+  static const double present = 0.0;
+  // a product along mu: nvec stacked vectors, groups, blocks of a stacked factor
+  enum { PLAIN, RULE, ALWAYS };
+  auto product = [&](int mu, int nvec, int groups, int blocks, int form) {
+    const int n = op->n[mu];
+    const bool last = mu == last_axis(op);
+    GemmArgs g{};
+    for (int i = 0; i < groups; ++i) g.Ff[i] = form == PLAIN ? nullptr : &present;
+    g.groups = groups;
+    g.fold_blocks = blocks;
+    g.K = n * blocks;
+    g.b_trans = mu > 0;
+    if (mu == 0) {
+      g.M = (int)(op->dof / n) * nvec;
+      g.N = g.lda = g.ldc = n;
+      g.inner = 1;
+    } else {
+      g.M = n;
+      g.N = g.ldb = g.ldc = last ? (int)(op->dof / n) : op->n[0];
+      g.inner = last ? nvec : nvec * op->n[2];
+      g.sB = (int64_t)g.K * g.N;
+      g.sC = (int64_t)n * g.N;
+    }
+    g.fold = form == ALWAYS ? 2 : 1;
+    if (form == RULE && groups > 1) g.fold = group_fold(g);
+    return product_us(g);
+  };
+  // a transform of nvec vectors and its inverse of one; an action by G node products
+  auto transforms = [&](int nvec, int form) {
+    double us = 0.0;
+    for (int mu = 0; mu < op->d; ++mu)
+      us += (mu == 0 ? product(0, 1, nvec, 1, form) : product(mu, nvec, 1, 1, form)) + product(mu, 1, 1, 1, form);
+    return us;
+  };
+  auto nodes = [&](int G) {
+    double us = product(last_axis(op), 1, 1, G, RULE);
+    for (int mu = 0; mu + 1 < op->d; ++mu) us += product(mu, 1, G, 1, RULE);
+    return us;
+  };
+  const int first = op->scheme == MM_ETD2RK ? 2 : 1, stages = op->scheme == MM_EE ? 1 : 2;
+  auto step = [&](int form) { return transforms(first, form) + (stages == 2 ? transforms(1, form) : 0.0); };
+  constexpr double margin = 1.05;   // (for the estimates: wrong by up to 9 % of a step then)
+  if (op->q == 0) return margin * step(ALWAYS) < step(PLAIN);
+  const double scale = 2.6 + 1.5e-6 * (double)op->dof;
+  return margin * (step(ALWAYS) + stages * scale) < nodes(op->q + first - 1) + nodes(op->q);
 }
 
 // T1 <- transform of `count` grid functions (T1, T2: count stacked vectors each)
@@ -1653,12 +1712,13 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
     }
   }
 
-  // ERK on such axes throughout: the folded sine basis (axes of one length share it: A_mu
-  // depends on n_mu alone)
+  // ERK on such axes throughout, where it pays: the folded sine basis (axes of one length share
+  // it: A_mu depends on n_mu alone)
   if (family == MM_ERK && prec == MM_FP64 && !periodic) {
     op->sine = true;
     for (int mu = 0; mu < op->d; ++mu) op->sine = op->sine && op->bc[mu] == MM_BC_DIRICHLET && op->beta_bar[mu] == 0.0;
   }
+  op->sine = op->sine && sine_pays(op);
   if (op->sine) {
     SineNodes nodes{};
     nodes.q = op->q;

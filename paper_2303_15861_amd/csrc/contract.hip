@@ -998,6 +998,29 @@ bool use_fold(const GemmArgs& g, int prec) {
   return g.fold == 2 || (g.fold == 1 && fold_regs_pays(g, 1)) || fold_tiles(g) >= kFoldMinTiles;
 }
 
+// (per kernel: start, chain of one tile over k, rounds of tiles, traffic; least-squares fit to the
+// ERK steps and phi1 actions of 99 grids with axes of 6 to 1300 points, 8 % rms)
+double product_us(const GemmArgs& g) {
+  const int G = fold_blocks(g), n = g.K / G, f = n - n / 2;
+  const int64_t fibers = g.b_trans ? g.N : g.M, count = (int64_t)g.inner * g.groups;
+  const double units = (double)((fibers + 15) / 16 * count), bytes = 8.0 * n * (double)(fibers * count);
+  if (use_fold(g, MM_FP64)) {
+    const int ld = fold_ld(n);
+    if (fold_regs_fits(g)) {
+      const double slow = (f > 64 && f <= 96 ? 0.7 : 0.0) + (f > 64 && f <= 128 && ld % 16 == 0 ? 0.9 : 0.0);
+      return 4.4 + 3.7 * (0.01 * f + slow) + 1e-5 * f * units * ((f + 15) / 16) + 3.8e-7 * bytes;
+    }
+    const double rounds = std::max(1.0, (double)(fold_tiles(g) * g.groups) / 512);
+    return 5.0 + 0.16 * G * ld * rounds + 1.9e-7 * (1 + G) * bytes;
+  }
+  if (plain_regs_fits(g)) return 4.7 + 6e-7 * bytes;
+  const int T = choose_tile(g, MM_FP64);
+  const double tiles = (double)((g.M + T - 1) / T) * ((g.N + T - 1) / T) * (double)count;
+  if (T == 128) return 0.39 * g.K * tiles / kFillSlots;
+  if (T == 64) return 11.0 + (0.07 + 0.2 * std::max(0.0, tiles / (3 * kComputeUnits) - 1)) * g.K;
+  return 3.3 + 0.035 * g.K;
+}
+
 hipError_t launch_gemm(int prec, GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.inner <= 0 || g.groups <= 0 || g.groups > kMaxGroups)
     return hipErrorInvalidValue;

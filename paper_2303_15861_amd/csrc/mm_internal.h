@@ -263,6 +263,8 @@ hipError_t launch_plain_regs(GemmArgs& g, hipStream_t s);
 // 128-tiles would not fill the chip once, and in FP64 32 when 64-tiles would not give
 // every compute unit one).
 int choose_tile(const GemmArgs& g, int prec);
+// Estimated time of an FP64 launch (us).
+double product_us(const GemmArgs& g);
 // MM_SLICED mode product (64 x 64 tiles; factor operand as digit planes).
 hipError_t launch_gemm_sliced(GemmArgs& g, hipStream_t s);
 // MM_SLICED chained mode product: C (M x F per fiber group) = F_mu (M x K) . V^T, with the
