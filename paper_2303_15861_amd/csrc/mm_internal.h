@@ -256,7 +256,7 @@ bool fold_regs_fits(const GemmArgs& g);
 // plain product.
 bool fold_regs_pays(const GemmArgs& g, int groups);
 hipError_t launch_fold_regs(GemmArgs& g, hipStream_t s);
-// Plain FP64 products of the same kind, square factors of at most 64 points.
+// Plain FP64 products of the same kind, square factors of 17 to 64 points.
 bool plain_regs_fits(const GemmArgs& g);
 hipError_t launch_plain_regs(GemmArgs& g, hipStream_t s);
 // Tile size the launcher takes for g in precision prec (g.tile if set, else 64 when

@@ -567,7 +567,6 @@ bool offsets_fit(const GemmArgs& g) {
 template <int BT>
 hipError_t launch_plain_bt(GemmArgs& g, hipStream_t s) {
   switch ((g.K + 15) / 16) {
-    case 1:
     case 2: return launch_regs_h<BT, 0, 4>(g, s);
     case 3: return launch_regs_h<BT, 0, 6>(g, s);
     case 4: return launch_regs_h<BT, 0, 8>(g, s);
@@ -577,11 +576,12 @@ hipError_t launch_plain_bt(GemmArgs& g, hipStream_t s) {
 
 }  // namespace
 
-// Plain products of square factors of 2 to 64 points: the tiled kernel walks a serial chain of
+// Plain products of square factors of 17 to 64 points: the tiled kernel walks a serial chain of
 // K chunks, each with its load latency on a launch this small; here all of K is loaded at
-// once.
+// once. Up to 16 points the tiled kernel has a single chunk and is no slower (a phi1 action on
+// 16^3 by six products and a scaling 18.9 us in a replayed graph, 20.6 with this kernel).
 bool plain_regs_fits(const GemmArgs& g) {
-  return g.fold_blocks <= 1 && g.K >= 2 && g.K <= 64 && (g.b_trans ? g.M : g.N) == g.K && (!g.b_trans || g.N >= 2) &&
+  return g.fold_blocks <= 1 && g.K >= 17 && g.K <= 64 && (g.b_trans ? g.M : g.N) == g.K && (!g.b_trans || g.N >= 2) &&
          g.sA == 0 && !g.in_f32 && !g.out_f32 && offsets_fit(g);
 }
 
