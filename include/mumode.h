@@ -283,10 +283,13 @@ mm_status mm_timing_read(mm_ctx* ctx, int kind, int64_t* launches, double* total
  * tests). tile = 0 (default): 128 x 128 tiles, or 64 x 64 when a launch has fewer
  * 128-tiles than the chip holds at once, or in FP64 32 x 32 when it has fewer 64-tiles
  * than the chip has compute units; 32, 64 or 128 force that size (32 applies to FP64
- * launches, the other precisions take 64 then). FP64 results are bit-identical across
- * tile sizes (every output's sum over k runs in the same order); in the other precisions
- * 64 and 128 agree likewise. Other values: MM_EINVAL. Takes effect for launches enqueued
- * after the call. */
+ * launches, the other precisions take 64 then). A forced size also keeps the separate
+ * launches where the default runs several FP64 products of one grid in one (x3 slabs of
+ * grids with n1, n2 <= 64, and periodic 2D grids of up to 256 points per axis); folded
+ * products have no such tile. FP64 products are bit-identical across tile sizes (every
+ * output's sum over k runs in the same order), and so are exponential actions; steps that
+ * leave such a launch agree to rounding. In the other precisions 64 and 128 agree
+ * likewise. Other values: MM_EINVAL. Takes effect for launches enqueued after the call. */
 mm_status mm_set_gemm_tile(mm_ctx* ctx, int tile);
 
 /* Small 2D Lawson solves (n1, n2 <= 64, FP64, Lawson-Euler or Lawson2b) run their whole
@@ -313,11 +316,13 @@ mm_status mm_set_sliced_chain(mm_ctx* ctx, int mode);
  * y = E x splits into the sums and differences of mirrored entries of x and two products
  * with half-size factors, at half the multiply-adds; the results agree with the plain
  * product to rounding. Applies to the exp actions of the Lawson and ERK steps and of
- * mumode_expv. mode = 0: off; 1 (default): on for axes of 17 to 256 points (with few
- * tiles 17 to 512) and for products with at least 192 folded tiles (128 grid rows or
- * columns x 64 folded positions) per problem; 2: always. ERK operators with such axes
- * throughout then run their actions in the folded sine basis, and one-workgroup 2D solves
- * fold too; mumode_expv on small grids stays plain. The decision does not depend on how
+ * mumode_expv. mode = 0: off; 1 (default): on where it is the faster form: axes of 17 to
+ * 256 points (from 129 on with enough fibers; with few tiles up to 512 points) and
+ * products with at least 192 folded tiles (128 grid rows or columns x 64 folded positions)
+ * per problem; 2: always, and the products of an x3 slab as separate ones. ERK operators
+ * with such axes throughout run their actions in the folded sine basis unless the mode is
+ * 0, where that is estimated to be faster at setup, and one-workgroup 2D solves fold too;
+ * mumode_expv on small grids stays plain in mode 1. The decision does not depend on how
  * many problems share a launch. Other modes: MM_EINVAL. */
 mm_status mm_set_fold(mm_ctx* ctx, int mode);
 

@@ -428,6 +428,10 @@ void set_fold(const mm_op* op, GemmArgs& g, int mu, const PassIO& io) {
   if (g.fold == 1 && g.groups > 1) g.fold = group_fold(g);
 }
 
+// Whether the caller's settings ask for separate products where the default runs those along x1 and
+// x2 in one launch: a product tile, and fold mode 2 (that launch has plain products)
+bool separate_products(const mm_op* op) { return op->ctx && (op->ctx->gemm_tile != 0 || op->ctx->fold == 2); }
+
 // Whether the product of nvec stacked vectors along axis mu >= 1 (factor j, rows of ld values) is
 // one of the tiled kernels (FP64): longer than the register-held plain kernel takes, and not on
 // the register-held folded one
@@ -1934,9 +1938,9 @@ mm_status mumode_expv(mm_ctx* ctx, const mm_op* op, int j, const double* in, dou
   // small grids keep the plain products, whose sums are those of mumode_expv_noalloc (it has
   // no folded factors): the two agree bit for bit on every grid that the latter takes
   const Layout dense{0, 0};
-  if (op->prec == MM_FP64 && !op->periodic && ctx->gemm_tile == 0 &&
+  if (op->prec == MM_FP64 && !op->periodic && !separate_products(op) &&
       slab_fits(op->d, op->n[0], op->n[1], op->n[2])) {
-    // (as mumode_expv_noalloc; a product tile set by the caller keeps the separate products)
+    // (as mumode_expv_noalloc)
     HIPCHK(ctx, timed_launch(ctx, MM_KIND_FUSED, 2.0 * (double)op->dof * (op->n[0] + op->n[1]), s, [&] {
       return launch_slab_action(in, factor(op, 0, j), factor(op, 1, j), t0, op->n[0], op->n[1], op->n[2], s);
     }));
@@ -2002,7 +2006,7 @@ namespace {
 // bits (eight problems: 108 against 89 us per step with the slab kernel, whose workgroups
 // hold a compute unit each).
 bool slab_active(const mm_op* op) {
-  return op->family == MM_LAWSON && op->prec == MM_FP64 && !op->periodic &&
+  return op->family == MM_LAWSON && op->prec == MM_FP64 && !op->periodic && !separate_products(op) &&
          (op->scheme == MM_SLE || op->scheme == MM_LAWSON2A || op->scheme == MM_SL2) &&
          slab_fits(op->d, op->n[0], op->n[1], op->n[2]);
 }
@@ -2123,9 +2127,11 @@ mm_status enqueue_lawson_slab(mm_ctx* ctx, const mm_op* op, double* u, int nstep
 // (periodic.hip): FP64, flux form, axes of at most 256 points. The remainder's two axes, the
 // operator's part of F and independent actions share launches, every pointwise pass is an
 // epilogue: a step of the stabilised Lawson2 has eight launches on one stream instead of
-// forty on two (256^2, Sec. 5.1: 261 -> 60 us).
+// forty on two (256^2, Sec. 5.1: 261 -> 60 us). A product tile set by the caller keeps the
+// separate launches.
 bool periodic_active(const mm_op* op) {
-  return op->periodic && op->prec == MM_FP64 && op->form == MM_FORM_FLUX && periodic_fits(op->d, op->n[0], op->n[1]);
+  return op->periodic && op->prec == MM_FP64 && (!op->ctx || op->ctx->gemm_tile == 0) &&
+         op->form == MM_FORM_FLUX && periodic_fits(op->d, op->n[0], op->n[1]);
 }
 
 hipError_t periodic_tasks(const mm_op* op, const PeriodicTask* t, int count, hipStream_t s) {
