@@ -234,9 +234,11 @@ mm_status mumode_phi1v(mm_ctx* ctx, const mm_op* op, const double* in, double* o
  * n1*n2*n3 <= 2^21 (2,097,152 grid values), else MM_EINVAL with a message. The scratch is
  * fully written before it is read in every call, so no state carries over, but every
  * call on one device shares it: calls that overlap in time on one device (on different
- * streams or threads) race, and the caller must serialise them. Results are
- * bit-identical to mumode_expv with the same factors. Enqueued on `stream`;
- * MM_EDEVICE if a launch fails. */
+ * streams or threads) race, and the caller must serialise them. The products are plain
+ * ones: results are bit-identical to mumode_expv with the same factors where its products
+ * are plain too (mm_set_fold mode 0; axes with advection in A or a Neumann end; by default
+ * every product of fewer than 192 folded tiles, so cubes up to the limit) and agree with it
+ * to rounding elsewhere. Enqueued on `stream`; MM_EDEVICE if a launch fails. */
 mm_status mumode_expv_noalloc(mm_ctx* ctx, int d, const int* n, const double* const* E, const double* in,
                               double* out, void* stream);
 
@@ -322,8 +324,8 @@ mm_status mm_set_sliced_chain(mm_ctx* ctx, int mode);
  * per problem; 2: always, and the products of an x3 slab as separate ones. ERK operators
  * with such axes throughout run their actions in the folded sine basis unless the mode is
  * 0, where that is estimated to be faster at setup, and one-workgroup 2D solves fold too;
- * mumode_expv on small grids stays plain in mode 1. The decision does not depend on how
- * many problems share a launch. Other modes: MM_EINVAL. */
+ * products of mumode_expv with fewer than 192 folded tiles stay plain in mode 1. The
+ * decision does not depend on how many problems share a launch. Other modes: MM_EINVAL. */
 mm_status mm_set_fold(mm_ctx* ctx, int mode);
 
 /* Step replay through HIP graphs (launch-bound small problems). steps = 0 (default):
