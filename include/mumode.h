@@ -325,7 +325,10 @@ mm_status mm_set_sliced_chain(mm_ctx* ctx, int mode);
  * with such axes throughout run their actions in the folded sine basis unless the mode is
  * 0, where that is estimated to be faster at setup, and one-workgroup 2D solves fold too;
  * products of mumode_expv with fewer than 192 folded tiles stay plain in mode 1. The
- * decision does not depend on how many problems share a launch. Other modes: MM_EINVAL. */
+ * decision does not depend on how many problems share a launch. Setting mode 0 builds what
+ * the context's quadrature operators in the sine basis need without it (2 (q + 1) grid
+ * functions and the stacked factors each): MM_ENOMEM if that fails, with the mode
+ * unchanged. Other modes: MM_EINVAL. */
 mm_status mm_set_fold(mm_ctx* ctx, int mode);
 
 /* Step replay through HIP graphs (launch-bound small problems). steps = 0 (default):

@@ -1126,6 +1126,52 @@ hipError_t chain_action(const mm_op* op, int j, int nvec, double* out, Layout lo
 }
 
 
+// The stacked last-axis factors of an ERK quadrature, stage 1 (ETD2RK [E(1) | tau w_j E(theta_j)],
+// ERK2P1 [tau w_j E(theta_j)]), stage 2 ([tau/2 w_j E(theta_j)]) and phi1 ([w_j E(theta_j)])
+mm_status stack_factors(mm_op* op, hipStream_t st) {
+  const int q = op->q, la = last_axis(op), nl = op->n[la], g1 = (op->scheme == MM_ETD2RK) ? q + 1 : q;
+  const double tau = op->tau;
+  mm_ctx* ctx = op->ctx;
+  mm_status rc;
+  if ((rc = dev_alloc(op, &op->f3_stage1, (int64_t)nl * g1 * nl)) != MM_OK) return rc;
+  if ((rc = dev_alloc(op, &op->f3_stage2, (int64_t)nl * q * nl)) != MM_OK) return rc;
+  if ((rc = dev_alloc(op, &op->f3_phi, (int64_t)nl * q * nl)) != MM_OK) return rc;
+  int col = 0;
+  if (op->scheme == MM_ETD2RK) {
+    HIPCHK(ctx, launch_place_scaled(op->f3_stage1, g1 * nl, 0, factor(op, la, 0), nl, 1.0, st));
+    col = nl;
+  }
+  // sliced mode: unweighted blocks (the weights scale the first pass instead)
+  const bool unit = op->prec == MM_SLICED;
+  for (int j = 1; j <= q; ++j) {
+    HIPCHK(ctx, launch_place_scaled(op->f3_stage1, g1 * nl, col + (j - 1) * nl, factor(op, la, j), nl,
+                                    unit ? 1.0 : tau * op->weight[j], st));
+    HIPCHK(ctx, launch_place_scaled(op->f3_stage2, q * nl, (j - 1) * nl, factor(op, la, j), nl,
+                                    unit ? 1.0 : 0.5 * tau * op->weight[j], st));
+    HIPCHK(ctx, launch_place_scaled(op->f3_phi, q * nl, (j - 1) * nl, factor(op, la, j), nl,
+                                    unit ? 1.0 : op->weight[j], st));
+  }
+  return MM_OK;
+}
+
+// What an ERK quadrature in the sine basis needs for its plain form. On failure nothing is left
+// allocated.
+mm_status build_plain(mm_op* op, hipStream_t st) {
+  mm_status rc = stack_factors(op, st);
+  for (int i = 0; i < 2 && rc == MM_OK; ++i) rc = dev_alloc(op, &op->plain_t[i], (op->q + 1) * op->dof);
+  if (rc == MM_OK && hipStreamSynchronize(st) != hipSuccess) {
+    set_err(op->ctx, "the plain form of an ERK operator failed on the device");
+    rc = MM_EDEVICE;
+  }
+  op->plain = rc == MM_OK;
+  if (op->plain) return MM_OK;
+  for (double** p : {&op->f3_stage1, &op->f3_stage2, &op->f3_phi, &op->plain_t[0], &op->plain_t[1]}) {
+    dev_free(op, *p);
+    *p = nullptr;
+  }
+  return rc;
+}
+
 mm_status check_op(mm_ctx* ctx, const mm_op* op) {
   if (!ctx) return MM_EINVAL;
   if (!op) {
@@ -1214,6 +1260,8 @@ void mumode_destroy(mm_op* op) {
     return;
   }
   hipSetDevice(op->ctx->device);
+  auto& lean = op->ctx->lean;
+  lean.erase(std::remove(lean.begin(), lean.end(), op), lean.end());
   dev_free(op, op->a);
   for (size_t i = 0; i < op->fac.size(); ++i)
     if (op->fac_owned[i]) dev_free(op, op->fac[i]);
@@ -1253,6 +1301,7 @@ void mumode_destroy(mm_op* op) {
   }
   if (op->spec_fork) hipEventDestroy(op->spec_fork);
   for (int i = 0; i < 6; ++i) dev_free(op, op->buf[i]);
+  for (int i = 0; i < 2; ++i) dev_free(op, op->plain_t[i]);
   dev_free(op, op->vdig);
   dev_free(op, op->vexp);
   dev_free(op, op->vdig2);
@@ -1761,30 +1810,10 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
       if (lens[i] > 0 && (rc = dev_alloc(op, &op->buf[i], lens[i])) != MM_OK) return fail(rc);
     }
   } else if (family == MM_ERK) {
-    const int q = op->q;
-    // stage 1: ETD2RK [E(1) | tau w_j E(theta_j)], ERK2P1 [tau w_j E(theta_j)]
-    const int g1 = (scheme == MM_ETD2RK) ? q + 1 : q;
-    if ((rc = dev_alloc(op, &op->f3_stage1, (int64_t)nl * g1 * nl)) != MM_OK) return fail(rc);
-    if ((rc = dev_alloc(op, &op->f3_stage2, (int64_t)nl * q * nl)) != MM_OK) return fail(rc);
-    if ((rc = dev_alloc(op, &op->f3_phi, (int64_t)nl * q * nl)) != MM_OK) return fail(rc);
-    int col = 0;
-    if (scheme == MM_ETD2RK) {
-      HIPCHK(ctx, launch_place_scaled(op->f3_stage1, g1 * nl, 0, factor(op, la, 0), nl, 1.0, st));
-      col = nl;
-    }
-    // sliced mode: unweighted blocks (the weights scale the first pass instead)
-    const bool unit = prec == MM_SLICED;
-    for (int j = 1; j <= q; ++j) {
-      HIPCHK(ctx, launch_place_scaled(op->f3_stage1, g1 * nl, col + (j - 1) * nl, factor(op, la, j), nl,
-                                      unit ? 1.0 : tau * op->weight[j], st));
-      HIPCHK(ctx, launch_place_scaled(op->f3_stage2, q * nl, (j - 1) * nl, factor(op, la, j), nl,
-                                      unit ? 1.0 : 0.5 * tau * op->weight[j], st));
-      HIPCHK(ctx, launch_place_scaled(op->f3_phi, q * nl, (j - 1) * nl, factor(op, la, j), nl,
-                                      unit ? 1.0 : op->weight[j], st));
-    }
+    const int q = op->q, g1 = (scheme == MM_ETD2RK) ? q + 1 : q;
+    if (!op->sine && (rc = stack_factors(op, st)) != MM_OK) return fail(rc);
     // the stacked factors' blocks are weighted exp factors of the last axis: they fold
-    // where that axis's factors do (in the sine basis none is used: without it, at fold mode 0,
-    // nothing folds)
+    // where that axis's factors do
     if (prec == MM_FP64 && op->ffold[la] && !op->sine) {
       const int64_t fb = (int64_t)2 * (nl - nl / 2) * fold_ld(nl);
       if ((rc = dev_alloc(op, &op->f3_stage1_fold, fb * g1)) != MM_OK) return fail(rc);
@@ -1812,12 +1841,14 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
       HIPCHK(ctx, convert(d2, op->f3_stage2_exp, op->f3_stage2, nl, q * nl, q * nl));
       HIPCHK(ctx, convert(d3, op->f3_phi_exp, op->f3_phi, nl, q * nl, q * nl));
     }
-    // buffers: 0 g0, 1 T1 ((q+1) dof), 2 T2 ((q+1) dof), 3 U, 4 D, 5 F0 (ERK2P1)
-    const int64_t lens[6] = {dof, (q + 1) * dof, (q + 1) * dof, dof, dof, scheme == MM_ERK2P1 ? dof : 0};
+    // buffers: 0 g0, 1 T1 and 2 T2 (q + 1 grid functions, in the sine basis 2), 3 U, 4 D, 5 F0 (ERK2P1)
+    const int64_t t = op->sine ? 2 * dof : (q + 1) * dof;
+    const int64_t lens[6] = {dof, t, t, dof, dof, scheme == MM_ERK2P1 ? dof : 0};
     for (int i = 0; i < 6; ++i) {
       op->buf_len[i] = lens[i];
       if (lens[i] > 0 && (rc = dev_alloc(op, &op->buf[i], lens[i])) != MM_OK) return fail(rc);
     }
+    if (op->sine && ctx->fold == 0 && (rc = build_plain(op, st)) != MM_OK) return fail(rc);
   } else {
     // buffers: 0 and 1 hold two stacked grid functions each; stabilized Lawson2 needs a
     // fifth grid function (buffer 2). Lawson-Euler and Lawson2b on finite differences keep
@@ -1883,6 +1914,7 @@ mm_status mumode_setup(mm_ctx* ctx, const mm_problem* prob, double tau, int fami
     set_err(ctx, "setup failed on the device");
     return fail(MM_EDEVICE);
   }
+  if (op->sine && op->q > 0 && !op->plain) ctx->lean.push_back(op);   // (built when fold mode 0 is set)
   *out = op;
   return MM_OK;
 }
@@ -1989,7 +2021,8 @@ mm_status mumode_phi1v(mm_ctx* ctx, const mm_op* op, const double* in, double* o
   }
   double w[kMaxGroups];
   HIPCHK(ctx, grouped_action(op, op->q, ins, fidx, stacked(op, 3), stacked_exp(op, 3), out, nullptr, 0.0,
-                                 op->buf[1], op->buf[2], s, stage_weights(op, 3, w)));
+                             op->sine ? op->plain_t[0] : op->buf[1], op->sine ? op->plain_t[1] : op->buf[2], s,
+                             stage_weights(op, 3, w)));
   return MM_OK;
 }
 
@@ -2572,8 +2605,8 @@ mm_status enqueue_erk(mm_ctx* ctx, const mm_op* op, double* u, int nsteps, hipSt
   if (op->exact) return enqueue_erk_exact(ctx, op, u, nsteps, s);
   const double tau = op->tau;
   const int q = op->q;
-  double *g0 = op->buf[0], *T1 = op->buf[1], *T2 = op->buf[2], *U = op->buf[3], *D = op->buf[4],
-         *F0 = op->buf[5];
+  double *g0 = op->buf[0], *T1 = op->sine ? op->plain_t[0] : op->buf[1],
+         *T2 = op->sine ? op->plain_t[1] : op->buf[2], *U = op->buf[3], *D = op->buf[4], *F0 = op->buf[5];
   const double* ins[kMaxGroups];
   int fidx[kMaxGroups];
   double w1[kMaxGroups], w2[kMaxGroups];
@@ -3103,6 +3136,19 @@ mm_status mm_set_fold(mm_ctx* ctx, int mode) {
   if (mode < 0 || mode > 2) {
     set_err(ctx, "fold mode must be 0, 1 or 2");
     return MM_EINVAL;
+  }
+  if (mode == 0 && !ctx->lean.empty()) {
+    // on the setup stream, also while the caller records a graph
+    HIPCHK(ctx, hipSetDevice(ctx->device));
+    hipStreamCaptureMode capture = hipStreamCaptureModeRelaxed;
+    HIPCHK(ctx, hipThreadExchangeStreamCaptureMode(&capture));
+    mm_status rc = MM_OK;
+    while (rc == MM_OK && !ctx->lean.empty()) {
+      rc = build_plain(ctx->lean.back(), ctx->stream);
+      if (rc == MM_OK) ctx->lean.pop_back();
+    }
+    HIPCHK(ctx, hipThreadExchangeStreamCaptureMode(&capture));
+    if (rc != MM_OK) return rc;
   }
   ctx->fold = mode;
   return MM_OK;

@@ -436,6 +436,7 @@ struct mm_ctx {
   std::vector<mm_timed> timed;
   size_t timed_used = 0;
   std::vector<mm_batch_ws> bws;   // per stream: grouped sliced launches
+  std::vector<mm_op*> lean;       // live operators without their plain forms (mm_op::plain)
 };
 
 struct mm_op {
@@ -498,6 +499,10 @@ struct mm_op {
   int* f3_stage1_exp = nullptr;
   int* f3_stage2_exp = nullptr;
   int* f3_phi_exp = nullptr;
+  // ERK quadrature in the sine basis: the stacked factors and the scratch of the node products
+  // (T1, T2: q + 1 grid functions each), which fold mode 0 alone uses; built when it is set
+  bool plain = false;
+  double* plain_t[2] = {nullptr, nullptr};
   double* buf[6] = {nullptr};          // scratch
   int64_t buf_len[6] = {0};
   // Lawson-Euler and Lawson2b keep their stage vectors (buf[0], buf[1]) with x1 rows of

@@ -54,3 +54,73 @@ def test_route(mm, n, scheme, q, sine):
         # the exact forms differ in their bits only where the route differs
         assert np.array_equal(got[0], got[1]) == (not sine)
     assert np.max(np.abs(got[1] - got[0])) <= FP64_TOL * np.max(np.abs(got[0]))
+
+
+def test_plain_form_is_built_on_demand(mm):
+    """Fold mode 0 gives operators in the sine basis their node products, those set up before it and
+    under it alike: the same bits of phi1 actions and steps. A graph recorded before keeps its
+    results."""
+    import torch
+    n, q = (97, 96, 98), 7
+    p = synth.constant_problem(n, 66, a_const=0.5, tau=1e-4, scheme="etd2rk", q=q, beta=(0.1,) * 3, r=synth.R_CUBIC)
+
+    def results(op):
+        u = torch.from_numpy(p.u0).cuda()
+        out = torch.empty_like(u)
+        mm.mumode_phi1v(op, u, out)
+        mm.step(op, u, 2)
+        return u.cpu().numpy(), out.cpu().numpy()
+
+    late, early = mm.Context(0), mm.Context(0)
+    early.set_fold(0)
+    op = mm.setup_problem(late, p)
+    sine = results(op)
+    g, u = torch.cuda.CUDAGraph(), torch.from_numpy(p.u0).cuda()
+    with torch.cuda.graph(g):
+        mm.step(op, u, 2)
+    late.set_fold(0)
+    plain = results(op)
+    ref = results(mm.setup_problem(early, p))
+    for a, b, c in zip(plain, ref, sine):
+        assert np.array_equal(a, b)
+        assert np.max(np.abs(a - c)) <= FP64_TOL * np.max(np.abs(c))
+    late.set_fold(1)
+    again = results(op)
+    assert np.array_equal(again[0], sine[0]) and np.array_equal(again[1], sine[1])
+    for _ in range(3):
+        u.copy_(torch.from_numpy(p.u0))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(u.cpu().numpy(), sine[0])
+    op.close()
+    late.set_fold(0)
+    late.close()
+    early.close()
+
+
+def test_memory_of_an_operator_in_the_sine_basis():
+    """It holds seven grid functions and the coefficient, not the scratch of the node products
+    (2 (q + 1) grid functions) as well: free memory around a setup, in a process of its own (freed
+    memory stays in the device's pool)."""
+    import os
+    import subprocess
+    import sys
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    code = """
+import torch, synth, paper_2303_15861_amd as mm
+n = (130, 131, 132)
+p = synth.constant_problem(n, 67, a_const=0.5, tau=1e-4, scheme="etd2rk", q=7, beta=(0.1,) * 3)
+ctx = mm.Context(0)
+free = torch.cuda.mem_get_info()[0]
+op = mm.setup_problem(ctx, p)
+torch.cuda.synchronize()
+print((free - torch.cuda.mem_get_info()[0]) / (8 * n[0] * n[1] * n[2]))
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    # (also in it: the operator's factors and the test's own copy of the coefficient; with the
+    # node products' scratch it is above 22)
+    assert float(r.stdout.split()[-1]) < 14
