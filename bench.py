@@ -212,15 +212,22 @@ def roofline(kern, prec, p):
     kname = max(("gemm_k", "gemm_n", "stencil", "fused"), key=lambda k: kern[k]["total_ms"])
     k = kern[kname]
     secs = k["total_ms"] * 1e-3
-    if kname == "fused":
+    if kname == "fused" and p.d == 2 and not any(b == 2 for b in getattr(p, "bc", ())):
         # one workgroup per solve on one compute unit: its share of the FP64 matrix peak
         roof = {"bound": "mfma", "achieved": k["work"] / secs / 1e12, "peak": PEAK["fp64"] / 256 / 1e12,
                 "unit": "TFLOP/s", "scope": "one compute unit"}
+    elif kname == "fused":
+        # launches over the whole chip: the products of an x3 slab, or tasks of a periodic grid
+        roof = {"bound": "mfma", "achieved": k["work"] / secs / 1e12, "peak": PEAK["fp64"] / 1e12, "unit": "TFLOP/s"}
     elif kname == "stencil":
         # algorithmic bytes per grid point of a fused remainder pass: read u and a, write
-        # two outputs (first pass) or read U, W, a and write u (second pass): 32 B
-        roof = {"bound": "hbm", "achieved": 32.0 * k["work"] / secs / 1e9, "peak": HBM_PEAK / 1e9,
-                "unit": "GB/s"}
+        # two outputs (first pass) or read U, W, a and write u (second pass): 32 B. A launch of
+        # two passes (last stage of a step and first of the next) counts its points twice and
+        # reads U, W, a and writes two outputs: 40 B.
+        dof = float(np.prod(p.n))
+        pairs = k["work"] / dof - k["launches"]
+        roof = {"bound": "hbm", "achieved": dof * (40.0 * pairs + 32.0 * (k["launches"] - pairs)) / secs / 1e9,
+                "peak": HBM_PEAK / 1e9, "unit": "GB/s"}
     elif prec.startswith("sliced"):
         # int8 digit products executed, S(S+1)/2 per algorithmic multiply-add. Chained
         # Lawson steps (every axis of 129..256 points under the default chain mode): each
@@ -248,7 +255,8 @@ def roofline(kern, prec, p):
                 roof["plain_equivalent_tflops"] = plain / secs / 1e12
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["kernel"] = {"gemm_k": "gemm (mode 1)", "gemm_n": "gemm (modes 2, 3)", "stencil": "stencil",
-                      "fused": "whole small-2D solve in one workgroup (one compute unit)"}[kname]
+                      "fused": "whole small-2D solve in one workgroup (one compute unit)" if "scope" in roof
+                               else "products and stage work of x3 slabs or periodic tasks"}[kname]
     roof["avg_launch_us"] = k["avg_us"]
     return roof, kname
 
