@@ -482,12 +482,15 @@ struct Shape {
   static constexpr int LATE = RT >= 5 && RT <= 8;
 };
 
-// Outputs are stored past the caches, except small ones that a tiled product reads next: on few
-// tiles its chain of K chunks waits for each load. Along 2700 points after 65 (1.4 MB) it takes
-// 98 us on cached values and 118 on streamed ones; along 4000 after 176 (5.6 MB) the Lawson-Euler
-// step takes 188 and 206. Large outputs gain nothing from the caches (255^3 Lawson2b steps 635 us
-// streamed, 647 cached).
-constexpr int64_t kCachedBytes = 6 << 20;
+// Outputs are stored past the caches, with two exceptions. Small ones that a tiled product reads
+// next: on few tiles its chain of K chunks waits for each load. Along 2700 points after 65 (1.4 MB)
+// it takes 98 us on cached values and 118 on streamed ones; along 4000 after 176 (5.6 MB) the
+// Lawson-Euler step takes 188 and 206. And large ones in rows that begin and end inside 128-byte
+// lines, whose parts would go to memory one by one: an exponential action on 255^3 takes 333 us
+// streamed and 269 cached, on 191^3 151 and 125, on 143^3 (23 MB) 71 and 67; 110^3 (11 MB) ETD2RK
+// steps 202 and 209, 127^3 254 in either form. Large outputs in whole lines gain nothing from the
+// caches (255^3 Lawson2b steps 635 us streamed, 647 cached).
+constexpr int64_t kCachedBytes = 6 << 20, kPartialLineBytes = 16 << 20;
 
 template <int BT, int FOLD, int H>
 hipError_t launch_regs_h(GemmArgs& g, hipStream_t s) {
@@ -508,7 +511,8 @@ hipError_t launch_regs_h(GemmArgs& g, hipStream_t s) {
   g.tiles_n = (int)W;
   g.total = (int)(RG * W * g.groups);
   g.per_xcd = (g.total + 7) / 8;
-  g.stream_out = !g.chunked_next || 8 * units * 16 * n * g.groups > kCachedBytes;
+  const int64_t bytes = 8 * units * 16 * n * g.groups;
+  g.stream_out = !(g.chunked_next && bytes <= kCachedBytes) && !(g.ldc % 16 != 0 && bytes > kPartialLineBytes);
   gemm_f64_regs<BT, FOLD, H, S::RW, S::WC, S::NC, S::WPE, S::LATE><<<dim3(8 * g.per_xcd), dim3(64 * S::RW * S::WC), 0, s>>>(g);
   return hipGetLastError();
 }
