@@ -513,7 +513,8 @@ hipError_t launch_regs_h(GemmArgs& g, hipStream_t s) {
   g.per_xcd = (g.total + 7) / 8;
   const int64_t bytes = 8 * units * 16 * n * g.groups;
   g.stream_out = !(g.chunked_next && bytes <= kCachedBytes) && !(g.ldc % 16 != 0 && bytes > kPartialLineBytes);
-  gemm_f64_regs<BT, FOLD, H, S::RW, S::WC, S::NC, S::WPE, S::LATE><<<dim3(8 * g.per_xcd), dim3(64 * S::RW * S::WC), 0, s>>>(g);
+  const auto kernel = gemm_f64_regs<BT, FOLD, H, S::RW, S::WC, S::NC, S::WPE, S::LATE>;
+  kernel<<<dim3(8 * g.per_xcd), dim3(64 * S::RW * S::WC), 0, s>>>(g);
   return hipGetLastError();
 }
 

@@ -560,10 +560,10 @@ hipError_t launch_stencil_batch(int d, const StencilArgs* a, int count, hipStrea
 // points, TP apart, of the run widened by one row on either side, where it computes u+; the
 // neighbours along x1 and x2 of U and a are read from LDS (two planes of each, loaded one
 // plane ahead), those of u+ likewise from LDS one plane later, and what lies along x3
-// (U, u+, faces) stays in the thread's registers. 255^3: 180 us against 2 x 119 for the two launches
-// (440 MB read, 290 MB written: not the traffic but about 120 vector instructions a point, 63 of
+// (U, u+, faces) stays in the thread's registers. 255^3: 174 us against 2 x 119 for the two launches
+// (432 MB read, 284 MB written: not the traffic but about 120 vector instructions a point, 63 of
 // them arithmetic, and two barriers a plane bound it; loading two planes ahead gained nothing).
-// 127^3 29 against 2 x 17.5, 130 x 129 x 127 33 against 2 x 26.
+// 127^3 28 against 2 x 17, 130 x 129 x 127 33 against 2 x 26.
 // Every access to memory is a buffer access with the plane's size, at an offset past it where a
 // lane has nothing to load or store: no branch splits the loads in flight.
 // loads of a thread per run
@@ -804,11 +804,11 @@ static bool pair_accepts(const StencilArgs& a) {
   return !a.nondiv && !a.sub && !a.dig && !a.out0f && !a.out1f && !a.neu[0] && !a.neu[1] && !a.neu[2] && a.ldi == a.ldo;
 }
 
-// Where the one launch is the faster: its estimate against that of two launches of stencil_batch_kernel (7 ns per 1000 lanes, idle ones included),
-// 3 us for each launch, and a margin for the estimates. Measured per step, two launches -> one: 63^3
-// 28.7 -> 29.0 us (stays), 96^3 56 -> 53.5, 110^3 81 -> 73, 127^3 95 -> 88.5, 130 x 129 x 127
-// 126 -> 106, 160^3 191 -> 162, 210^3 430 -> 359, 255^3 685 -> 614, 30 x 200 x 150 76 -> 63,
-// 200 x 30 x 150 67 -> 63.5.
+// Where the one launch is the faster: its estimate against that of two launches of
+// stencil_batch_kernel (7 ns per 1000 lanes, idle ones included), 3 us for each launch, and a margin
+// for the estimates. Measured per step, two launches -> one: 63^3 28.7 -> 29.0 us (stays), 96^3
+// 56 -> 53.5, 110^3 81 -> 73, 127^3 95 -> 88.5, 130 x 129 x 127 126 -> 106, 160^3 191 -> 162,
+// 210^3 430 -> 359, 255^3 685 -> 614, 30 x 200 x 150 76 -> 63, 200 x 30 x 150 67 -> 63.5.
 bool stencil_pair_pays(int d, const StencilArgs& a, int count) {
   if (d != 3 || !pair_accepts(a)) return false;
   int P;

@@ -43,8 +43,8 @@ def actions(mm, n, fold, tiles=(0, 32, 64)):
     return outs
 
 
-@pytest.mark.parametrize("n", [(2, 2, 2), (2, 64, 1), (15, 17, 3), (31, 31, 31), (33, 16, 40), (64, 63, 20), (64, 64, 64),
-                               (48, 5, 180)])
+@pytest.mark.parametrize("n", [(2, 2, 2), (2, 64, 1), (15, 17, 3), (31, 31, 31), (33, 16, 40), (64, 63, 20),
+                               (64, 64, 64), (48, 5, 180)])
 def test_slab_action_bits(mm, n):
     outs = actions(mm, n, 1)
     assert all(np.array_equal(o, outs[0]) for o in outs)

@@ -61,7 +61,8 @@ def run(mm, probs, steps):
 @pytest.mark.parametrize("n,scheme,kinds", [((16, 12, 9), "l2b", ALL),
                                             ((20, 18, 16), "l2b", ("plain", "nondiv", "plain")),
                                             ((96, 96, 96), "l2b", ("plain", "nondiv")),
-                                            ((33, 34, 35), "l2b", ALL), ((40, 5, 63), "le", ALL), ((17, 16, 70), "l2b", ALL),
+                                            ((33, 34, 35), "l2b", ALL), ((40, 5, 63), "le", ALL),
+                                            ((17, 16, 70), "l2b", ALL),
                                             ((90, 70), "l2b", ALL), ((130, 70), "le", ALL),
                                             ((129, 130, 40), "l2b", ("advected", "plain")),
                                             ((40, 33), "l2b", ALL), ((63, 16), "le", ALL),
