@@ -100,6 +100,38 @@ def test_plain_form_is_built_on_demand(mm):
     early.close()
 
 
+def test_plain_form_is_built_while_a_graph_is_recorded(mm):
+    """Fold mode 0 set between two steps of a recorded graph: the first replays in the sine basis, the
+    second by nodes, as the same calls do directly."""
+    import torch
+    p = synth.constant_problem((97, 96, 98), 68, a_const=0.5, tau=1e-4, scheme="etd2rk", q=7, beta=(0.1,) * 3)
+    results = []
+    for record in (False, True):
+        ctx = mm.Context(0)
+        op = mm.setup_problem(ctx, p)
+        u = torch.from_numpy(p.u0).cuda()
+
+        def steps():
+            mm.step(op, u, 1)
+            ctx.set_fold(0)
+            mm.step(op, u, 1)
+
+        if record:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                steps()
+            for _ in range(2):
+                u.copy_(torch.from_numpy(p.u0))
+                g.replay()
+                torch.cuda.synchronize()
+                results.append(u.cpu().numpy())
+        else:
+            steps()
+            results.append(u.cpu().numpy())
+        ctx.close()
+    assert all(np.array_equal(r, results[0]) for r in results)
+
+
 def test_memory_of_an_operator_in_the_sine_basis():
     """It holds seven grid functions and the coefficient, not the scratch of the node products
     (2 (q + 1) grid functions) as well: free memory around a setup, in a process of its own (freed
